@@ -374,7 +374,8 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
         const int ch = t >> 3, sub = t & 7;
         const int nn = n0 + ch;
         const int f = nn < a.N ? a.wfmt[nn] : CHAM_W_NFMT;
-        const bool ok = f < CHAM_W_NFMT && ((a.mask >> f) & 1u);
+        // a group search of non-finite weights selects nothing (group size 0): no valid format
+        const bool ok = f < CHAM_W_NFMT && ((a.mask >> f) & 1u) && !(a.gsel && gsz == 0);
         // the block metadata of every enabled kind is read without waiting for the format
         // (it is zero for channels of other formats), so these loads overlap the format load
         float mxf = 0.0f;
@@ -422,7 +423,7 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
             c.colscale = ldexpf(1.0f, c.eref);
         } else if (ok) {
             c.fmt = f;
-            c.zero = a.wzero[nn];
+            c.zero = a.wzero ? a.wzero[nn] : 0.0f;  // group-scaled weights (an MX format here) have none
             if (f == CHAM_W_NF4) {
                 // levels (|v| <= 1) times the block absmax over 2^eref stay below 2^15, and a
                 // block 2^-28 below the largest is still a normal half-precision number

@@ -197,3 +197,38 @@ def test_group_gemm_every_choice():
                 Yr, Bm = oracle.linear(xh, Wh)
                 rel = np.abs(Y - Yr) / np.maximum(Bm, 1e-300)
                 assert rel.max() <= 1e-3, (gsz, f, rel.max())
+
+
+@pytest.mark.parametrize("f", [cham.W_MXINT4, cham.W_MXFP4])
+def test_group_gemm_mx_choice(f):
+    """The group-scaled GEMM where an MX format is chosen: its blocks carry the scales, and
+    there are no per-channel scales or zero points to read."""
+    g = np.random.default_rng(7)
+    N, K, M = 200, 320, 130
+    W, _ = synth.hetero_weights(95, N, K)
+    X = (g.standard_t(4, (M, K)) * 0.7).astype(np.float32)
+    gq, ref = _gsearch_both(W, np.ones(K, np.float32), 1 << f, 1, packed=True)
+    assert _assert_gsearch_equal(gq, ref) and tuple(_np(gq.choice)) == (32, f)
+    Wh = oracle.dequant_grouped(ref, K)
+    xq = cham.quantize_act(torch.from_numpy(X).to(DEV), cham.A_FP8_E4M3, dynamic=True)
+    _, _, xh, _, _ = oracle.quantize_act_dynamic(X, cham.A_FP8_E4M3, want_xhat=True)
+    Yr, Bm = oracle.linear(xh, Wh)
+    for packed in (gq.packed, None):
+        case(f"mixed_linear_grouped MX choice f={f} packed={packed is not None}")
+        Y = _np(cham.mixed_linear_grouped(xq, cham.GWQ(**{**gq.__dict__, "packed": packed}))).astype(np.float64)
+        assert np.all(np.abs(Y - Yr) <= 1e-3 * Bm + 1e-300), f
+
+
+def test_group_search_of_non_finite_weights_selects_nothing():
+    """An infinite weight (outside the contract) makes every tuple's error NaN: no tuple is
+    selected, and the packing pass and the GEMM take the weight as having no format."""
+    N, K, M = 70, 320, 40
+    W, _ = synth.hetero_weights(96, N, K)
+    W[3, 5] = -np.inf
+    for packed in (True, False):
+        case(f"select_group_formats non-finite packed={packed}")
+        gq = cham.select_group_formats(torch.from_numpy(W).to(DEV), torch.ones(K, device=DEV), cham.MASK_DIT_W4,
+                                       want_packed=packed)
+        assert _np(gq.choice)[0] == 0
+        xq = cham.quantize_act(torch.ones(M, K, device=DEV), cham.A_FP8_E4M3)
+        assert np.all(_np(cham.mixed_linear_grouped(xq, gq)) == 0.0)
