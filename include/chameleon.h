@@ -130,11 +130,12 @@ typedef struct cham_wq {
                                1e-5; -1 for disabled formats); NULL = skip                    */
     void* packed;           /* cham_packed_bytes(N, K) bytes, 256-byte aligned: the weights in
                                the layout cham_mixed_linear consumes (per channel its format
-                               parameters; per (64-wide k-step, channel, half) its codes and a
-                               16-entry decode table).  Written by the search when non-NULL
-                               (K must then be a multiple of 64); cham_mixed_linear reads it
-                               instead of deriving it from the codes on every call.  It must
-                               come from the search that wrote these codes.  NULL = skip.      */
+                               parameters; the weights decoded to half precision in the order
+                               of the matrix-core operand, 2 bytes each).  Written by the
+                               search when non-NULL (K must then be a multiple of 64);
+                               cham_mixed_linear reads it instead of deriving it from the
+                               codes on every call.  It must come from the search that wrote
+                               these codes, by the same library version.  NULL = skip.       */
 } cham_wq;
 
 /* Search the formats of W [N][K] (device, binary32, finite) and fill *wq's buffers.

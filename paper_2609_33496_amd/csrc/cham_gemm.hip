@@ -2,40 +2,41 @@
 // weight format (Sec. 4.5) and one activation format per call (Sec. 4.3).
 //
 // Per-channel formats do not map onto one native MFMA operand type (Sec. 6), so the
-// weights are dequantized on the fly into a common half-precision operand.  Every 4-bit
-// code of every format is an entry of a 16-value decode table per (k-step of 64, channel,
-// half k-step of 32): base value (NF4 level, E2M1 value, integer, q - z) times the block
-// factor (NF4 block absmax, MX 2^E) relative to the channel's largest block, rounded to
-// binary32 and then to half precision.  A pre-pass packs, per (k-step, channel, half), the
-// codes and this table (two byte planes) into one record (layout in cham_records.h); the
-// main kernel decodes with v_perm_b32, so every 4-bit format decodes with the same
-// instructions.  Integers, E2M1 values and MX mantissas are exact in half precision; NF4
-// levels times their block absmax carry the two roundings (relative error <= 2^-11 +
-// 2^-24).  8-bit integer formats are decoded arithmetically
-// (1024 + c trick, exact) with parameters from the same table slot.
+// weights are brought to a common half-precision operand: base value (NF4 level, E2M1 value,
+// integer, q - z) times the block factor (NF4 block absmax, MX 2^E) relative to the channel's
+// largest block, rounded to binary32 and then to half precision.  Integers, E2M1 values and MX
+// mantissas are exact in half precision; NF4 levels times their block absmax carry the two
+// roundings (relative error <= 2^-11 + 2^-24).  The packing pass decodes every weight once --
+// 4-bit codes through a 16-entry table per (k-step of 64, channel, half) and v_perm_b32, 8-bit
+// integers arithmetically (1024 + c trick, exact) -- into the lane layout of the MFMA operand
+// (cham_records.h), 2 bytes per weight.  Decoding in the main loop instead (1.5 bytes per
+// weight read, about 200 VALU instructions per k-step and wavefront beside 32 MFMAs) took
+// 65.2 us on 2048 x 10240 x 1280 (now 55.8) and, with 8-bit codes, 153 us on
+// 8192 x 4608 x 1152 (now 87).
 //
 // Activations in a per-tensor format (INT8, E4M3, E5M2) are decoded to half precision
 // while they are staged into LDS (exact); MX activations are decoded by a pre-pass into a
 // half-precision copy relative to the row's largest block exponent, with a row scale.
 //
-// Main kernel: BM x 256 output tiles (BM = 256, 128 or 64), or 128 x 128 for layers whose
-// full-width tiles leave CUs idle; k-steps of 64; four wavefronts that each own BM rows x
-// 32 TN channels (BM/32 x TN blocks of v_mfma_f32_32x32x16_f16, binary32 accumulation), so
-// a decoded weight feeds BM/32 MFMAs per k sub-step.
-// Activation tiles and weight records go global -> registers with coalesced 16-byte
-// buffer loads one or more k-steps ahead (deeper register rings for the short steps of
-// small tiles); the activation tile is stored into one of two LDS buffers with its
-// 16-byte chunks XOR-swizzled per row pair, so all LDS accesses are free of bank
-// conflicts, and the weight records stay in registers.  Barriers fence LDS only, so the
-// prefetch stays in flight across them.  Layers with too few output tiles to fill the
+// Main kernel: 128 x 256, 128 x 128 or 64 x 128 output tiles; k-steps of 64; four wavefronts
+// side by side that each own all the tile's rows x 32 TN channels (blocks of
+// v_mfma_f32_32x32x16_f16, binary32 accumulation).  What bounds it: on long layers power (a
+// 4096 x 4096 x 16384 product runs at 1314 TFLOP/s with the matrix cores busy 74 % of the
+// cycles at 1.65 GHz, as the library's dense f16 product does, 1290), on short ones the rounds
+// of tiles that do not fill the chip and the output write.  Per k-step a 128 x 64 wavefront
+// block reads 16 KB from LDS and 8 KB from L1 for 1024 MFMA cycles per SIMD, about half of
+// either's rate; the 128 x 32 block reads twice as much LDS per MFMA, and three of them per
+// SIMD hide latency better.
+// Weights go from memory straight to the operand registers (coalesced 16-byte buffer loads, a
+// step or two ahead); activation tiles go global -> registers -> one of two LDS buffers, with
+// their 16-byte chunks XOR-swizzled per row pair.  Barriers fence LDS only, so the loads in
+// flight stay in flight across them.  Layers with too few output tiles to fill the
 // CUs split k over several workgroups that write partial outputs, summed in split order
 // by a second kernel; every output element is produced by plain stores (no atomics), so
 // results do not depend on scheduling.
 //
 // The MFMA contracts over k in any order as long as both operands agree: lane half h of a
-// k-step takes k = 32h .. 32h+31, sub-step s the 8 k at 32h + 8s, and with two codes per
-// byte those 8 values come in the order (0,4,1,5,2,6,3,7); the activation operand is
-// staged with its columns in that same order.
+// k-step takes k = 32h .. 32h+31, sub-step s the 8 k at 32h + 8s.
 #include <atomic>
 #include <cmath>
 #include <vector>
@@ -51,9 +52,10 @@ typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float16v __attribute__((ext_vector_type(16)));
 
 constexpr int BK = 64;
-constexpr int kThreads = 256;
-// TN = 32-channel MFMA blocks per wavefront: a tile is 128 TN channels wide (four wavefronts)
-constexpr int tile_width(int TN) { return 128 * TN; }
+// TN = 32-channel MFMA blocks per wavefront, NW wavefronts side by side
+constexpr int tile_width(int TN, int NW) { return 32 * TN * NW; }
+// 16-byte chunks of a block of 32 channels in one k-step of the packed weights
+constexpr int kBlockChunks = 256;
 constexpr int kBufferFlags = 0x00020000;  // buffer descriptor word 3: 32-bit data, raw
 constexpr int kStoreNonTemporal = 2;      // cache-policy operand of a buffer store: nt
 
@@ -66,7 +68,6 @@ struct PrepArgs {
     const uint8_t* xe8;
     int afmt;
     int M, K;
-    int perm4;  // 1: store each group of 8 columns in the order 0,4,1,5,2,6,3,7
     _Float16* Xh;
     float* rowscale;
 };
@@ -99,16 +100,8 @@ __global__ __launch_bounds__(256) void prep_kernel(PrepArgs p) {
                                                : ldexpf((float)(int8_t)c, kb - 6 - eref);
         }
         half8 h;
-        if (p.perm4) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[2 * j] = (_Float16)v[j];
-                h[2 * j + 1] = (_Float16)v[j + 4];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
-        }
+        for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
         *reinterpret_cast<half8*>(out + 8 * g) = h;
     }
     if (threadIdx.x == 0) p.rowscale[m] = ldexpf(1.0f, eref);
@@ -126,7 +119,6 @@ struct PrepConvArgs {
     const uint8_t* xe8;
     int afmt;
     int B, H, W, C;
-    int perm4;
     const float* xs;  // per-sample scale / zero point (per-tensor formats)
     const float* xz;
     int rps;          // rows (pixels) per sample
@@ -184,23 +176,15 @@ __global__ __launch_bounds__(256) void prep_conv_kernel(PrepConvArgs p) {
             }
         }
         half8 h;
-        if (p.perm4) {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                h[2 * j] = (_Float16)v[j];
-                h[2 * j + 1] = (_Float16)v[j + 4];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
-        }
+        for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
         *reinterpret_cast<half8*>(out + 8 * g) = h;
     }
     if (threadIdx.x == 0) p.rowscale[m] = mx ? ldexpf(1.0f, eref) : ldexpf(p.xs[m / p.rps], eref);
 }
 
 // ------------------------------------------------------------------------------------
-// weight decode in the main kernel
+// weight decode
 // ------------------------------------------------------------------------------------
 
 // Look up 4 codes (one per byte, values 0..15); returns the low and high bytes.
@@ -220,20 +204,24 @@ union H8 {
     uint32_t u[4];
 };
 
-// 8 codes of one sub-step from a word of 8 nibbles -> order (0,4,1,5,2,6,3,7)
+// 8 codes from a word of 8 nibbles
 CHAM_DEV half8 decode_nibbles(const Table& t, uint32_t w) {
     uint32_t lo_e, hi_e, lo_o, hi_o;
     lookup4(t, w & 0x0F0F0F0Fu, lo_e, hi_e);         // k = 0, 2, 4, 6
     lookup4(t, (w >> 4) & 0x0F0F0F0Fu, lo_o, hi_o);  // k = 1, 3, 5, 7
+    const uint32_t l01 = __builtin_amdgcn_perm(lo_o, lo_e, 0x05010400u);  // low bytes of k0..k3
+    const uint32_t l23 = __builtin_amdgcn_perm(lo_o, lo_e, 0x07030602u);  // k4..k7
+    const uint32_t h01 = __builtin_amdgcn_perm(hi_o, hi_e, 0x05010400u);
+    const uint32_t h23 = __builtin_amdgcn_perm(hi_o, hi_e, 0x07030602u);
     H8 r;
-    r.u[0] = __builtin_amdgcn_perm(hi_e, lo_e, 0x06020400u);  // k0, k4
-    r.u[1] = __builtin_amdgcn_perm(hi_o, lo_o, 0x06020400u);  // k1, k5
-    r.u[2] = __builtin_amdgcn_perm(hi_e, lo_e, 0x07030501u);  // k2, k6
-    r.u[3] = __builtin_amdgcn_perm(hi_o, lo_o, 0x07030501u);  // k3, k7
+    r.u[0] = __builtin_amdgcn_perm(h01, l01, 0x05010400u);
+    r.u[1] = __builtin_amdgcn_perm(h01, l01, 0x07030602u);
+    r.u[2] = __builtin_amdgcn_perm(h23, l23, 0x05010400u);
+    r.u[3] = __builtin_amdgcn_perm(h23, l23, 0x07030602u);
     return r.h;
 }
 
-// 8 codes in natural order from two words of 4 byte-codes (4-bit formats in 8-bit layout)
+// 8 codes from two words of 4 byte-codes (4-bit formats in 8-bit layout)
 CHAM_DEV half8 decode_bytes_table(const Table& t, uint32_t w0, uint32_t w1) {
     uint32_t lo0, hi0, lo1, hi1;
     lookup4(t, w0, lo0, hi0);
@@ -268,8 +256,8 @@ CHAM_DEV half8 decode_bytes_int(const Table& t, uint32_t w0, uint32_t w1) {
 }
 
 // ------------------------------------------------------------------------------------
-// pre-pass 2: weight records (layout in cham_records.h), one per (k-step, channel, half
-// k-step): the half's codes (16 bytes at 4 bits, 32 at 8 bits), then its decode table
+// packing pass: weights in half precision (layout in cham_records.h), a record per (k-step,
+// channel, half k-step)
 // ------------------------------------------------------------------------------------
 struct RecArgs {
     const uint8_t* wfmt;
@@ -284,7 +272,7 @@ struct RecArgs {
     ColPrep* cols;
     float* colsum;  // [k-chunks][N] per workgroup chunk of k-steps: the sum of the channel's
                     // decoded weights (the GEMM adds the chunks in order)
-    uint4* rec;     // [K/64][N][2][pieces]
+    uint4* wh;      // half-precision weights [K/64][channel blocks][4][2][32] x 16 bytes
     // group-scaled weights (the DiT search): the chosen group size on the device (NULL: the
     // per-channel formats above), per-group scale / NF4 absmax and zero point [N][K/32]
     const int32_t* gsel;
@@ -335,7 +323,7 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
     const int64_t cstride = (int64_t)K * a.code_bits / 8;
 
     // this thread's records: channel n, half h, k-steps kb, kb + 4, ... below ke
-    const int n = n0 + ((t & 63) >> 1), h = t & 1;
+    const int n = n0 + (t & 31), h = (t >> 5) & 1;
     const bool live = n < a.N;
     const int kb = kc * a.kchunk + (t >> 6), ke = min(nst, (kc + 1) * a.kchunk);
     const int gsz = a.gsel ? *a.gsel : 0;  // group size of group-scaled weights, else 0
@@ -355,13 +343,6 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
             gz = 0.0f;
         }
         e8 = a.we8 ? (int)a.we8[(int64_t)n * (K / 32) + 2 * k + h] : 0;
-    };
-    auto store_rec = [&](int k, const uint4 (&code)[2], const Table& tb) __attribute__((always_inline)) {
-        uint4* dst = a.rec + (((int64_t)k * a.N + n) * 2 + h) * (cw + 2);
-        dst[0] = code[0];
-        if (cw > 1) dst[1] = code[1];
-        dst[cw] = make_uint4(tb.lo[0], tb.lo[1], tb.lo[2], tb.lo[3]);
-        dst[cw + 1] = make_uint4(tb.hi[0], tb.hi[1], tb.hi[2], tb.hi[3]);
     };
     uint4 pc[kRecPrefetch][2];
     float pn[kRecPrefetch], pz[kRecPrefetch];
@@ -446,16 +427,18 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
         }
     }
     __syncthreads();
-    const ColPrep c = cp[(t & 63) >> 1];
+    const ColPrep c = cp[t & 31];
     auto table = [&](float nfa, float gz, int e8) __attribute__((always_inline)) {
         return gsz && !is_mx(c.fmt) ? group_table(c, nfa, gz) : record_table(c, nfa, e8);
     };
-    // the sum of the record's decoded weights (the half-precision values the GEMM uses,
-    // relative to colscale), through the GEMM's own decode and binary32 dot products
+    // decode the half k-step's 32 weights, store them (sub-step q's 8 at chunk (q, h, channel)
+    // of the k-step's block: each wavefront's store is 1 KB in a row) and return their sum, the
+    // half-precision values relative to colscale added by binary32 dot products
     const bool int8c = a.code_bits == 8 && is_8bit(c.fmt);
-    auto record_sum = [&](const uint4 (&code)[2], const Table& tb) __attribute__((always_inline)) {
+    auto store_rec = [&](int k, const uint4 (&code)[2], const Table& tb) __attribute__((always_inline)) {
         float sum = 0.0f;
         const half2v one = {(_Float16)1.0f, (_Float16)1.0f};
+        uint4* dst = a.wh + ((int64_t)k * nblk + cb) * kBlockChunks + 32 * h + (t & 31);
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             H8 v;
@@ -467,6 +450,7 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
                 const uint32_t w0 = (q & 1) ? cc.z : cc.x, w1 = (q & 1) ? cc.w : cc.y;
                 v.h = int8c ? decode_bytes_int(tb, w0, w1) : decode_bytes_table(tb, w0, w1);
             }
+            dst[64 * q] = make_uint4(v.u[0], v.u[1], v.u[2], v.u[3]);
 #pragma unroll
             for (int r = 0; r < 4; ++r) sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, v.u[r]), one, sum, false);
         }
@@ -478,8 +462,7 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
         for (int i = 0; i < kRecPrefetch; ++i)
             if (kb + 4 * i < ke) {
                 const Table tb = table(pn[i], pz[i], pe[i]);
-                store_rec(kb + 4 * i, pc[i], tb);
-                psum += (double)record_sum(pc[i], tb);
+                psum += (double)store_rec(kb + 4 * i, pc[i], tb);
             }
         for (int k = kb + 4 * kRecPrefetch; k < ke; k += 4) {
             uint4 code[2];
@@ -487,8 +470,7 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
             int e8;
             load_rec(k, code, nfa, gz, e8);
             const Table tb = table(nfa, gz, e8);
-            store_rec(k, code, tb);
-            psum += (double)record_sum(code, tb);
+            psum += (double)store_rec(k, code, tb);
         }
     }
     // the channel's sum over this workgroup's k-steps: its 8 threads (2 halves x 4 k-phases)
@@ -499,7 +481,7 @@ __global__ __launch_bounds__(256) void record_kernel(RecBatch B) {
     if (t < kRecChannels && n0 + t < a.N) {
         double s2 = 0.0;
 #pragma unroll
-        for (int p = 0; p < 4; ++p) s2 += part[p][2 * t] + part[p][2 * t + 1];
+        for (int p = 0; p < 4; ++p) s2 += part[p][t] + part[p][t + 32];
         a.colsum[(int64_t)kc * a.N + n0 + t] = (float)(s2 * (double)cp[t].colscale);
     }
 }
@@ -516,7 +498,7 @@ CHAM_DEV void lds_barrier() {
 // main kernel
 // ------------------------------------------------------------------------------------
 struct GemmArgs {
-    const _Float16* Xh;      // [M][K] (column order as above), MX activation formats
+    const _Float16* Xh;      // [M][K], MX activation formats
     const float* rowscale;   // [M], MX activation formats
     const uint8_t* xc;       // [M][K] activation codes, per-tensor formats
     const float* xs;         // activation scale per sample [M / rps] (per-tensor formats)
@@ -525,12 +507,12 @@ struct GemmArgs {
     const ColPrep* cols;     // [N]
     const float* colsum;     // [nkc][N] per k-chunk sums of the decoded weights
     int nkc;
-    const uint4* rec;        // [K/64][N][2][pieces]
+    const uint4* wh;         // half-precision weights (layout in cham_records.h)
     float* Y;
     int M, N, K;
-    int row0, row1;  // rows [row0, row1) of this launch
     int tn;          // tile columns
-    int gm;          // tile rows per group of the XCD-aware tile order, 0: row-major (launch_gemm)
+    int gm;          // tile rows per group of the XCD-aware tile order, 0: row-major (group_rows)
+    int cached;      // 1: ordinary output stores, 0: non-temporal
     int splits;      // k-splits: workgroup b takes tile b % tiles and k-steps of split b / tiles
     int kchunk;      // k-steps per split
     float* part;     // splits > 1: [splits][M][N] partial outputs, summed by reduce_kernel
@@ -545,48 +527,44 @@ struct GemmArgs {
 // pre-pass's zero-padded half-precision copy, gathered per output pixel and tap.
 constexpr int kAF16 = 0, kAInt8 = 1, kAE4M3 = 2, kAE5M2 = 3, kAConv = 4;
 
-// 8 activation codes (k0..k3 in w0, k4..k7 in w1) -> 8 halves, in the order
-// (0,4,1,5,2,6,3,7) when perm4, else natural; exact for all three per-tensor formats.
+// 8 activation codes (k0..k3 in w0, k4..k7 in w1) -> 8 halves in that order; exact for all
+// three per-tensor formats.
 template <int AF>
-CHAM_DEV uint4 decode_act8(uint32_t w0, uint32_t w1, bool perm4, half2v negz) {
+CHAM_DEV uint4 decode_act8(uint32_t w0, uint32_t w1, half2v negz) {
     // byte selectors of v_perm_b32(w1, w0, sel): 0..3 -> k0..k3, 4..7 -> k4..k7, 12 -> 0
     uint32_t d[4];
     if (AF == kAE5M2) {  // E5M2 is the top byte of binary16
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t a = perm4 ? j : 2 * j, b = perm4 ? j + 4 : 2 * j + 1;
-            d[j] = __builtin_amdgcn_perm(w1, w0, 0x0Cu | (a << 8) | (0x0Cu << 16) | (b << 24));
-        }
+        for (int j = 0; j < 4; ++j)
+            d[j] = __builtin_amdgcn_perm(w1, w0, 0x0Cu | ((uint32_t)(2 * j) << 8) | (0x0Cu << 16) | ((uint32_t)(2 * j + 1) << 24));
     } else if (AF == kAE4M3) {  // hardware E4M3 -> binary16 conversion, unit scale
-        const uint32_t p0 = perm4 ? __builtin_amdgcn_perm(w1, w0, 0x05010400u) : w0;
-        const uint32_t p1 = perm4 ? __builtin_amdgcn_perm(w1, w0, 0x07030602u) : w1;
-        d[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p0, 1.0f, false));
-        d[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p0, 1.0f, true));
-        d[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p1, 1.0f, false));
-        d[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(p1, 1.0f, true));
+        d[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, false));
+        d[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, true));
+        d[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, false));
+        d[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, true));
     } else {  // INT8-asym: (1024 + c) - (1024 + z) in binary16
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint32_t a = perm4 ? j : 2 * j, b = perm4 ? j + 4 : 2 * j + 1;
-            const uint32_t v = __builtin_amdgcn_perm(w1, w0, a | (0x0Cu << 8) | (b << 16) | (0x0Cu << 24)) | 0x64006400u;
+            const uint32_t v = __builtin_amdgcn_perm(w1, w0, (uint32_t)(2 * j) | (0x0Cu << 8) | ((uint32_t)(2 * j + 1) << 16) | (0x0Cu << 24)) | 0x64006400u;
             d[j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, v) + negz);
         }
     }
     return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-template <int CODE_BITS, int TM, int AF, int TN>
-__global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4) ? 2 : 1) void gemm_kernel(GemmArgs a) {
+// NW wavefronts side by side, each TM x TN blocks of 32 x 32 outputs.
+template <int TM, int TN, int NW, int AF>
+__global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) void gemm_kernel(GemmArgs a) {
+    constexpr int NT = 64 * NW;
     constexpr int BM = 32 * TM;
-    constexpr int BN = tile_width(TN);
-    constexpr int CW = CODE_BITS / 4;  // 16-byte code pieces per record
-    constexpr int P = CW + 2;          // 16-byte pieces per record (codes + two table planes)
+    constexpr int BN = tile_width(TN, NW);
     constexpr bool HALF = AF == kAF16 || AF == kAConv;   // the operand comes in half precision
-    constexpr int AQ = HALF ? TM : (TM + 1) / 2;  // activation loads per thread per k-step
-    // codes: every load of the workgroup falls inside the tile (even TM), no range test
-    constexpr bool AFULL = HALF || AQ * kThreads == BM * 4;
-    constexpr int A_CH = BM * BK * 2 / 16;      // 16-byte chunks of an activation tile
-    __shared__ uint4 lds[2][A_CH];
+    constexpr int AL = BM * (HALF ? 8 : 4);              // 16-byte activation loads per k-step
+    constexpr int AQ = (AL + NT - 1) / NT;               // of them, per thread
+    constexpr bool AFULL = AQ * NT == AL;                // every load falls inside the tile
+    constexpr int ARH = HALF ? 8 : 4;                    // loads per row
+    constexpr int RSTEP = NT / ARH;                      // rows between a thread's loads
+    __shared__ uint4 lds[2][BM * 8];
     __shared__ __align__(16) float Rs[BM];
     __shared__ __align__(16) float Rc[AF == kAInt8 ? BM : 4];
 
@@ -594,14 +572,12 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
     const int lane = t & 63, wave = t >> 6;
     const int l32 = lane & 31, h = lane >> 5;
     const int K = a.K, N = a.N;
-    // Workgroup -> (split, tile).  gm = 0: tiles in row-major order, workgroup b taking
-    // tile b % tiles of split b / tiles.  gm > 0, the XCD-aware order: the dispatcher deals
-    // a launch's workgroups to the chip's 8 XCDs in turn (workgroup b runs on XCD b % 8, as
-    // its (b / 8)-th), and each XCD has its own L2, so each XCD takes a contiguous run of a
-    // logical order that walks groups of gm tile rows column by column: an XCD's tiles form
-    // a block of about gm rows by a few columns, whose activation rows and weight columns
-    // its L2 serves.  Both maps are bijections of [0, grid), whatever the grid.
-    const int mt = (a.row1 - a.row0 + BM - 1) / BM;
+    // Workgroup -> (split, tile).  gm = 0: tiles in row-major order.  gm > 0, the XCD-aware
+    // order: the dispatcher deals a launch's workgroups to the chip's 8 XCDs in turn (workgroup
+    // b runs on XCD b % 8, as its (b / 8)-th), and each XCD has its own L2, so each XCD takes a
+    // contiguous run of a logical order that walks groups of gm tile rows column by column.
+    // Both maps are bijections of [0, grid), whatever the grid.
+    const int mt = (a.M + BM - 1) / BM;
     const int tiles = mt * a.tn;
     const int G = (int)gridDim.x, b = (int)blockIdx.x, xcd = b & 7;
     const int lin = a.gm > 0 ? xcd * (G >> 3) + (xcd < (G & 7) ? xcd : (G & 7)) + (b >> 3) : b;
@@ -611,13 +587,13 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
         const int g0 = (tile / (a.gm * a.tn)) * a.gm;    // first tile row of the group
         const int gm = a.gm < mt - g0 ? a.gm : mt - g0;  // its tile rows (the last may be short)
         const int in = tile - g0 * a.tn;
-        m0 = a.row0 + (g0 + in % gm) * BM;
+        m0 = (g0 + in % gm) * BM;
         n0 = (in / gm) * BN;
     } else {
-        m0 = a.row0 + (tile / a.tn) * BM;
+        m0 = (tile / a.tn) * BM;
         n0 = (tile % a.tn) * BN;
     }
-    const int rows = a.row1 - m0 < BM ? a.row1 - m0 : BM;
+    const int rows = a.M - m0 < BM ? a.M - m0 : BM;
     // k-steps [kb, kb + nsteps) of this workgroup; the operand bases below start at kb
     const int kb = split * a.kchunk;
     const int nsteps = K / BK - kb < a.kchunk ? K / BK - kb : a.kchunk;
@@ -627,26 +603,25 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
     // clamped to [-1024, 1024] (exact in half precision); the rest z - z1 (an integer, exact
     // in binary32) is taken out in the epilogue as -(z - z1) s times the channel's weight sum
     // (split 0 only).
-    if (t < BM) {
-        const int m = t < rows ? m0 + t : m0;
+    for (int r = t; r < BM; r += NT) {
+        const int m = r < rows ? m0 + r : m0;
         if (HALF) {
-            Rs[t] = a.rowscale[m];
+            Rs[r] = a.rowscale[m];
         } else {
-            Rs[t] = a.xs[m / a.rps];
+            Rs[r] = a.xs[m / a.rps];
             if (AF == kAInt8) {
                 const float za = a.xz[m / a.rps], z1 = clampf(za, -1024.0f, 1024.0f);
-                Rc[t] = split == 0 ? -((za - z1) * a.xs[m / a.rps]) : 0.0f;
+                Rc[r] = split == 0 ? -((za - z1) * a.xs[m / a.rps]) : 0.0f;
             }
         }
     }
-    // the staging rows of this thread (row q >> 2 of load q = 256 i + t): their -(1024 + z1)
-    constexpr int AQ0 = HALF ? 1 : (TM + 1) / 2;
-    half2v negz[AQ0];
+    // the staging rows of this thread: their -(1024 + z1)
+    half2v negz[AF == kAInt8 ? AQ : 1];
 #pragma unroll
-    for (int i = 0; i < AQ0; ++i) {
+    for (int i = 0; i < (AF == kAInt8 ? AQ : 1); ++i) {
         negz[i] = half2v{(_Float16)0.0f, (_Float16)0.0f};
         if (AF == kAInt8) {
-            const int r = (i * 256 + t) >> 2;
+            const int r = t / ARH + RSTEP * i;
             const int m = r < rows ? m0 + r : m0;
             const _Float16 nz = (_Float16)(-(1024.0f + clampf(a.xz[m / a.rps], -1024.0f, 1024.0f)));
             negz[i] = half2v{nz, nz};
@@ -657,25 +632,24 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
     // through a buffer resource whose range check returns zeros past the last row.  The
     // tile is stored as rows of 8 logical 16-byte chunks (8 k each), chunk c of row r at
     // slot c ^ ((r >> 1) & 7).
-    //  half-precision copy: load q = 256 i + t is row q >> 3, chunk q & 7;
+    //  half-precision copy: load q = NT i + t is row q >> 3, chunk q & 7;
     //  codes: load q is row q >> 2, codes 16 (q & 3) .. + 15 = chunks 2 (q & 3), + 1.
-    const bool perm4 = CODE_BITS == 4;
     const __amdgpu_buffer_rsrc_t ra =
         AF == kAConv ? __builtin_amdgcn_make_buffer_rsrc((void*)a.Xh, (short)0, (int)a.xh_bytes, kBufferFlags)
         : AF == kAF16 ? __builtin_amdgcn_make_buffer_rsrc((void*)(a.Xh + (int64_t)m0 * K + kb * BK), (short)0,
                                                           (rows * K - kb * BK) * 2, kBufferFlags)
                       : __builtin_amdgcn_make_buffer_rsrc((void*)(a.xc + (int64_t)m0 * K + kb * BK), (short)0,
                                                           rows * K - kb * BK, kBufferFlags);
-    const uint32_t aoff0 = HALF ? (uint32_t)((t >> 3) * K * 2 + (((t & 7) ^ ((t >> 4) & 7)) << 4))
-                                : (uint32_t)((t >> 2) * K + ((t & 3) << 4));
-    // convolution: the padded pixel of each staging row (row (t >> 3) + 32 i) at tap (0, 0);
-    // rows past the tile's last take an offset past the buffer (loads return zeros)
+    const uint32_t acol = HALF ? (uint32_t)(((t & 7) ^ ((t >> 4) & 7)) << 4) : (uint32_t)((t & 3) << 4);
+    const uint32_t aoff0 = (uint32_t)((t / ARH) * K * (HALF ? 2 : 1)) + acol;
+    // convolution: the padded pixel of each staging row at tap (0, 0); rows past the tile's
+    // last take an offset past the buffer (loads return zeros)
     int pix[AF == kAConv ? AQ : 1];
 #pragma unroll
     for (int i = 0; i < (AF == kAConv ? AQ : 1); ++i) {
         pix[i] = -1;
         if (AF == kAConv) {
-            const int r = (t >> 3) + 32 * i;
+            const int r = t / ARH + RSTEP * i;
             if (r < rows) {
                 const int m = m0 + r, x = m % a.W, yb = m / a.W, y = yb % a.H, b = yb / a.H;
                 pix[i] = (b * (a.H + 2) + y) * (a.W + 2) + x;
@@ -695,12 +669,9 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
 #pragma unroll
         for (int i = 0; i < AQ; ++i) {
             uint32_t off;
-            if (AF == kAConv)
-                off = pix[i] < 0 ? 0x7FFFFFF0u
-                                 : (uint32_t)(((pix[i] + tapoff) * a.C + ci0) * 2) + (aoff0 - (uint32_t)((t >> 3) * K * 2));
-            else
-                off = HALF ? aoff0 + (uint32_t)(i * 64 * K + k * BK * 2) : aoff0 + (uint32_t)(i * 64 * K + k * BK);
-            S.v[i] = (!AFULL && i * 256 + t >= BM * 4)
+            if (AF == kAConv) off = pix[i] < 0 ? 0x7FFFFFF0u : (uint32_t)(((pix[i] + tapoff) * a.C + ci0) * 2) + acol;
+            else off = aoff0 + (uint32_t)(i * RSTEP * K + k * BK) * (HALF ? 2u : 1u);
+            S.v[i] = (!AFULL && i * NT + t >= AL)
                          ? make_uint4(0u, 0u, 0u, 0u)
                          : __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)off, 0, 0));
         }
@@ -708,74 +679,50 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
     auto store_a = [&](const AStage& S, int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < AQ; ++i) {
+            const int q = i * NT + t;
+            if (!AFULL && q >= AL) continue;
             if (HALF) {
-                lds[buf][i * 256 + t] = S.v[i];
+                lds[buf][q] = S.v[i];
             } else {
-                const int q = i * 256 + t;
-                if (AFULL || q < BM * 4) {
-                    const int r = q >> 2, c = 2 * (q & 3), sw = (r >> 1) & 7;
-                    lds[buf][r * 8 + (c ^ sw)] = decode_act8<AF>(S.v[i].x, S.v[i].y, perm4, negz[i]);
-                    lds[buf][r * 8 + ((c + 1) ^ sw)] = decode_act8<AF>(S.v[i].z, S.v[i].w, perm4, negz[i]);
-                }
+                const int r = q >> 2, c = 2 * (q & 3), sw = (r >> 1) & 7;
+                lds[buf][r * 8 + (c ^ sw)] = decode_act8<AF>(S.v[i].x, S.v[i].y, negz[AF == kAInt8 ? i : 0]);
+                lds[buf][r * 8 + ((c + 1) ^ sw)] = decode_act8<AF>(S.v[i].z, S.v[i].w, negz[AF == kAInt8 ? i : 0]);
             }
         }
     };
 
-    // ---- weight records of the lane's channels (column l32 of the wave's TN 32-channel
-    // blocks, half h): global -> registers one k-step ahead; past the last channel the
-    // range check returns zeros (zero codes, zero table)
-    const int nl = 32 * TN * wave + l32;
-    const int chans = N - n0 < BN ? N - n0 : BN;
-    const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.rec + ((int64_t)kb * N + n0) * 2 * P), (short)0, (int)(((int64_t)(K / BK - kb) * N - n0) * 2 * P * 16),
-        kBufferFlags);
-    const uint32_t rstep = (uint32_t)N * 2u * P * 16u;  // record bytes per k-step
-    struct Rec {
-        uint4 c[CW];
-        Table tb;
-    };
-    struct WStage {
-        Rec r[TN];
-    };
-    auto load_w = [&](WStage& W, int k) __attribute__((always_inline)) {
+    // ---- weights: the wave's TN blocks of 32 channels, straight from memory into the lane
+    // layout of the MFMA operand (1 KB per block and sub-step, consecutive over the lanes).
+    // Blocks past the last re-read the last one (their outputs are not stored).
+    const int nblk = (N + 31) >> 5;
+    const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(a.wh + (int64_t)kb * nblk * kBlockChunks), (short)0, -1, kBufferFlags);
+    const uint32_t wstep = (uint32_t)nblk * kBlockChunks * 16u;  // bytes per k-step
+    uint32_t wblk[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int col = nl + 32 * j;
-            const uint32_t off = col < chans ? (uint32_t)k * rstep + (uint32_t)((col * 2 + h) * P) * 16u : 0x7FFFFF00u;
-            uint4 v[P];
+    for (int j = 0; j < TN; ++j) {
+        const int blk = (n0 >> 5) + wave * TN + j;
+        wblk[j] = (uint32_t)__builtin_amdgcn_readfirstlane(blk < nblk ? blk : nblk - 1) * (kBlockChunks * 16u);
+    }
+    const int wlane = lane * 16;
+    auto load_w = [&](half8 (&W)[TN], int k, int s) __attribute__((always_inline)) {
 #pragma unroll
-            for (int q = 0; q < P; ++q)
-                v[q] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rr, (int)(off + 16u * q), 0, 0));
-#pragma unroll
-            for (int q = 0; q < CW; ++q) W.r[j].c[q] = v[q];
-            W.r[j].tb = Table{{v[CW].x, v[CW].y, v[CW].z, v[CW].w}, {v[CW + 1].x, v[CW + 1].y, v[CW + 1].z, v[CW + 1].w}};
-        }
+        for (int j = 0; j < TN; ++j)
+            W[j] = __builtin_bit_cast(half8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                 rw, wlane, (int)((uint32_t)k * wstep + wblk[j] + 1024u * (uint32_t)s), 0));
     };
 
-    // per-channel parameters of the lane's TN channels: 8-bit code layout decoded
-    // arithmetically, epilogue factor (loaded here, off the tail of the kernel)
-    bool int8[TN];
+    // per-channel epilogue factor (loaded here, off the tail of the kernel)
+    const int nl = 32 * TN * wave + l32;
     float cs[TN], csum[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int n = n0 + nl + 32 * j;
-        const ColPrep cp = n < N ? a.cols[n] : ColPrep{CHAM_W_NFMT, 0, 0.0f, 0.0f};
-        int8[j] = CODE_BITS == 8 && is_8bit(cp.fmt);
-        cs[j] = cp.colscale;
+        cs[j] = n < N ? a.cols[n].colscale : 0.0f;
         csum[j] = 0.0f;
         if (AF == kAInt8 && n < N)
             for (int q = 0; q < a.nkc; ++q) csum[j] += a.colsum[(int64_t)q * N + n];
     }
-    auto decode = [&](const Rec& r, int j, int s) __attribute__((always_inline)) -> half8 {
-        if (CODE_BITS == 4) {
-            const uint32_t w = s == 0 ? r.c[0].x : s == 1 ? r.c[0].y : s == 2 ? r.c[0].z : r.c[0].w;
-            return decode_nibbles(r.tb, w);
-        } else {
-            const uint4& cc = r.c[(s >> 1) & (CW - 1)];
-            const uint32_t w0 = (s & 1) ? cc.z : cc.x, w1 = (s & 1) ? cc.w : cc.y;
-            return int8[j] ? decode_bytes_int(r.tb, w0, w1) : decode_bytes_table(r.tb, w0, w1);
-        }
-    };
 
     // LDS chunk offset of the lane's activation operand in sub-step s (row l32 of block i
     // at + 256 i chunks)
@@ -791,92 +738,73 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
 
-    // ---- main loop.  Step k computes from LDS buffer k & 1.  At its start it stores the
-    // activation tile of step k + 1 (loaded DA steps earlier) into the other buffer and
-    // issues the loads of step k + 1 + DA (activations) and k + DW (weights) into register
-    // rings of DA and DW + 1 stages.  Short steps (64-row tiles) take deeper rings so the
-    // loads have more than one memory latency to arrive.  Half-width tiles keep 2-stage
-    // rings, which fit three workgroups per CU (at most 168 registers): with a 4-stage ring
-    // they fit two, which was 3-7 % faster than two workgroups with 2 stages, but three
-    // workgroups with 2 stages beat both (the QKV layers at 1280 4 % faster, the step 1 %,
-    // where the search shares the CUs).  Sub-steps 0-2 run with the
-    // operand reads and weight decode one sub-step ahead; then one barrier makes the new
-    // tile visible (and retires every read of this step's buffer), and the first operands
-    // of step k + 1 are read and decoded behind the MFMAs of sub-step 3.  Step indices past
-    // the end are clamped (harmless reloads); scheduling barriers keep the compiler from
-    // sinking the reads next to their uses.  The loop is unrolled by a multiple of both
-    // ring lengths and of the two LDS buffers, so every ring and buffer index is a constant.
-    constexpr int DW = TM == 2 ? 3 : 1;
-    constexpr int DA = TM == 2 ? 2 : 1;
-    constexpr int U = (DW + 1) > 2 ? (DW + 1) : 2;
-    static_assert(U % DA == 0 && U % 2 == 0, "the unrolled steps must repeat every ring and buffer index");
+    // ---- main loop.  Step k computes from LDS buffer k & 1 in four sub-steps of 16 k.  Each
+    // sub-step first issues its memory work -- the LDS reads of the activations LA sub-steps
+    // ahead and the reload of the weight registers that the previous sub-step has just used,
+    // with the same sub-step of step k + WD -- and then its MFMAs; scheduling barriers keep the
+    // two apart, so a weight register is reloaded WD steps before its next use and needs no
+    // second copy.  LA = 1: the activation tile of step k + 1 is decoded and stored to the
+    // other buffer behind the MFMAs of sub-step 1, and one barrier before the last sub-step
+    // makes it visible and retires every read of this step's buffer.  LA = 3 (tiles whose
+    // sub-step is two MFMAs, shorter than an LDS read): the reads of step k + 1 start at
+    // sub-step 1, behind the barrier, and the tile of step k + 2 is stored into this step's
+    // buffer in sub-step 2.  Step indices past the end are clamped (harmless reloads).
+    constexpr int LA = TM * TN <= 2 ? 3 : 1;
+    constexpr int WD = TM * TN <= (HALF ? 2 : 4) ? 2 : 1;
     const int klast = nsteps - 1;
-    AStage R[DA];
-    WStage W[DW + 1];
-    half8 af[TM], an[TM], bf[TN], bn[TN];
+    AStage R[2];
+    half8 fr[LA + 1][TM], W[WD][4][TN];
+    auto read_a = [&](half8 (&f)[TM], int buf, int s) __attribute__((always_inline)) {
 #pragma unroll
-    for (int d = 0; d < DW; ++d) load_w(W[d], d < klast ? d : klast);
+        for (int i = 0; i < TM; ++i) f[i] = __builtin_bit_cast(half8, lds[buf][i * 256 + aoff[s]]);
+    };
     load_a(R[0], 0);
-    store_a(R[0], 0);
 #pragma unroll
-    for (int d = 1; d <= DA; ++d) load_a(R[d % DA], d < klast ? d : klast);
+    for (int s = 0; s < 4; ++s) load_w(W[0][s], 0, s);
+    load_a(R[1], 1 < klast ? 1 : klast);
+    if (WD == 2) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) load_w(W[WD - 1][s], 1 < klast ? 1 : klast, s);
+    }
+    store_a(R[0], 0);
+    if (LA == 3) {
+        load_a(R[0], 2 < klast ? 2 : klast);
+        store_a(R[1], 1);
+    }
     lds_barrier();
 #pragma unroll
-    for (int i = 0; i < TM; ++i) af[i] = __builtin_bit_cast(half8, lds[0][i * 256 + aoff[0]]);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) bf[j] = decode(W[0].r[j], j, 0);
+    for (int s = 0; s < LA; ++s) read_a(fr[s], 0, s);
 
-    auto mfmas = [&]() __attribute__((always_inline)) {
+    auto step = [&](int k, int buf, AStage& Rn, AStage& Rl) __attribute__((always_inline)) {
+        const int kw = k + WD < klast ? k + WD : klast;
+        half8(&Wk)[4][TN] = W[WD == 2 ? buf : 0];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(af[i], bf[j], acc[i][j], 0, 0, 0);
-    };
-    auto step = [&](int k, int buf, const WStage& Wc, const WStage& Wn, WStage& Wl, AStage& Ra)
-                    __attribute__((always_inline)) {
-        if (k + 1 < nsteps) store_a(Ra, buf ^ 1);
-        load_a(Ra, k + 1 + DA < klast ? k + 1 + DA : klast);
-        load_w(Wl, k + DW < klast ? k + DW : klast);
-        const uint4* L = lds[buf];
-#pragma unroll
-        for (int s = 0; s < 3; ++s) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) an[i] = __builtin_bit_cast(half8, L[i * 256 + aoff[s + 1]]);
+        for (int s = 0; s < 4; ++s) {
+            if (s == 4 - LA) lds_barrier();
+            read_a(fr[(s + LA) % (LA + 1)], s + LA >= 4 ? buf ^ 1 : buf, (s + LA) & 3);
+            if (s > 0) load_w(Wk[s - 1], kw, s - 1);
+            if (s == 0) load_a(Rl, k + 1 + (LA + 1) / 2 < klast ? k + 1 + (LA + 1) / 2 : klast);
             __builtin_amdgcn_sched_barrier(0);
+            if (LA == 1 && s == 1) store_a(Rn, buf ^ 1);
+            if (LA == 3 && s == 2) store_a(Rn, buf);
 #pragma unroll
-            for (int j = 0; j < TN; ++j) bn[j] = decode(Wc.r[j], j, s + 1);
-            mfmas();
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fr[s % (LA + 1)][i], Wk[s][j], acc[i][j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[i] = an[i];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bf[j] = bn[j];
         }
-        lds_barrier();
-        const uint4* Ln = lds[buf ^ 1];
-#pragma unroll
-        for (int i = 0; i < TM; ++i) an[i] = __builtin_bit_cast(half8, Ln[i * 256 + aoff[0]]);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bn[j] = decode(Wn.r[j], j, 0);
-        mfmas();
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) af[i] = an[i];
-#pragma unroll
-        for (int j = 0; j < TN; ++j) bf[j] = bn[j];
+        load_w(Wk[3], kw, 3);
     };
+    // LA = 1: step k stores R[(k + 1) & 1] (tile k + 1) and loads tile k + 2 into R[k & 1];
+    // LA = 3: step k stores R[k & 1] (tile k + 2) and loads tile k + 3 into R[(k + 1) & 1]
+    constexpr int RN = LA == 1 ? 1 : 0;
     int k = 0;
-    for (; k + U <= nsteps; k += U) {
-#pragma unroll
-        for (int u = 0; u < U; ++u)
-            step(k + u, u & 1, W[u % (DW + 1)], W[(u + 1) % (DW + 1)], W[(u + DW) % (DW + 1)], R[(u + 1) % DA]);
+    for (; k + 2 <= nsteps; k += 2) {
+        step(k, 0, R[RN], R[RN ^ 1]);
+        step(k + 1, 1, R[RN ^ 1], R[RN]);
     }
-#pragma unroll
-    for (int u = 0; u + 1 < U; ++u)
-        if (k + u < nsteps)
-            step(k + u, u & 1, W[u % (DW + 1)], W[(u + 1) % (DW + 1)], W[(u + DW) % (DW + 1)], R[(u + 1) % DA]);
+    if (k < nsteps) step(k, 0, R[RN], R[RN ^ 1]);
 
     // ---- epilogue: 32x32 block, lane holds column l32, rows 8*(r/4) + 4*h + r%4; the
     // lane's 16 row scales of block i are 4 aligned float4 in LDS.  Stores go through a
@@ -884,12 +812,14 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
     // block, each row's offset a wave-uniform SGPR, and the range check drops the rows past
     // the last of a ragged tile (the lane skips columns past the last).  The output is not
     // read again here, so it is stored non-temporally (the L2 stays with the operand tiles
-    // other workgroups still read); k-split partials, which the reduction reads back at
-    // once, take ordinary stores.
+    // other workgroups still read).  Ordinary stores: k-split partials, which the reduction
+    // reads back at once, and outputs whose rows are not whole 128-byte lines (N % 32), where
+    // each line comes in pieces that only the L2 can put together (2430 x 9119 x 704: 45.8 us
+    // against 83.7 non-temporal).
     float* const out = a.splits > 1 ? a.part + (int64_t)split * a.M * N : a.Y;
     const __amdgpu_buffer_rsrc_t ro =
         __builtin_amdgcn_make_buffer_rsrc((void*)(out + (int64_t)m0 * N), (short)0, rows * N * 4, kBufferFlags);
-    const bool partial = a.splits > 1;
+    const bool cached = a.cached != 0;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
         float rs[16], rc[16];
@@ -914,7 +844,7 @@ __global__ __launch_bounds__(kThreads, TN == 1 ? 3 : (TM == 4 && CODE_BITS == 4)
                     if (AF == kAInt8) v = v + rc[r] * csum[j];
                     const uint32_t bits = __builtin_bit_cast(uint32_t, v);
                     const int soff = (8 * (r >> 2) + (r & 3)) * N * 4;
-                    if (partial) __builtin_amdgcn_raw_buffer_store_b32(bits, ro, voff, soff, 0);
+                    if (cached) __builtin_amdgcn_raw_buffer_store_b32(bits, ro, voff, soff, 0);
                     else __builtin_amdgcn_raw_buffer_store_b32(bits, ro, voff, soff, kStoreNonTemporal);
                 }
             }
@@ -957,11 +887,8 @@ __global__ __launch_bounds__(256) void reduce_kernel(const float* __restrict__ p
     }
 }
 
-// ---- launch plan.  A launch covers rows [row0, row1) with one tile shape.  The plan is
-// either one launch, optionally split along k into partial outputs that reduce_kernel
-// sums (for layers with too few output tiles to fill the CUs), or two launches of
-// different tile shapes: one for whole rounds of workgroups, the other for the rows left,
-// so the last round does not leave most CUs idle.
+// ---- launch plan: one launch of one tile shape, optionally split along k into partial
+// outputs that reduce_kernel sums (for layers with too few output tiles to fill the CUs).
 // CU count of the current device, queried once per device (every thread that races to
 // fill the cache stores the same value, so relaxed atomics suffice)
 int cu_count() {
@@ -976,164 +903,113 @@ int cu_count() {
     return n;
 }
 
-// Modeled time (us) of a launch of one tile shape, fitted to measurements on MI355X: one
-// fixed cost (prologue, output write) per launch -- the workgroups of later rounds start
-// while earlier ones finish -- plus the k-steps of the rounds of workgroups, each at the
-// k-step time of as many workgroups per CU as the round puts there.  Tiles 128 high fit two
-// workgroups on a CU, the half-width tile (128 x 128) three.
+// Modeled time (us) of a launch of one tile shape: a fixed cost (prologue, tail), plus the
+// k-steps of the rounds of workgroups, each at the k-step time of as many workgroups per CU as
+// the round puts there -- the workgroups of later rounds start while earlier ones finish --
+// plus the output.  The numbers are fitted to 1720 forced plans over 180 shapes (M 200 - 8192,
+// N 320 - 10240, K 640 - 5120) on MI355X, each timed behind its quantize call and again with
+// the last-level cache swept by other data; the planner's choice takes 1.0 % longer than the
+// best of the forced plans on average, 15 % at worst.  Tiles measured and not kept, as no shape
+// ran faster in them: 256 x 256 (one wavefront per SIMD: 84 us against 56 on
+// 2048 x 10240 x 1280), 64 x 256, and 128 x 128 and 64 x 128 of two wavefronts.
+constexpr int kMaxOcc = 4;
 struct TileCost {
-    int bm, tn, occ;                   // tile height, 32-channel blocks per wavefront, workgroups per CU
-    double step1, step2, step3, fixed;  // us: k-step with 1, 2, 3 workgroups on the CU; per launch
+    int tm, tn, nw, occ;   // 32-row blocks, 32-channel blocks per wavefront, wavefronts, workgroups per CU
+    double step[kMaxOcc];  // us: k-step with 1 .. occ workgroups on the CU
+    double fixed;          // us per launch
+    int bm() const { return 32 * tm; }
+    int bn() const { return tile_width(tn, nw); }
 };
-constexpr int kNumTiles = 4;
-constexpr TileCost kTileCosts[kNumTiles] = {{256, 2, 1, 2.13, 2.13, 2.13, 8.0},
-                                            {128, 2, 2, 1.21, 1.89, 1.89, 9.0},
-                                            {128, 1, 3, 0.715, 1.26, 1.64, 6.0},
-                                            {64, 2, 1, 0.82, 0.82, 0.82, 6.2}};
+constexpr int kNumTiles = 3;
+constexpr TileCost kTileCosts[kNumTiles] = {{4, 2, 4, 2, {0.812, 1.338}, 5.8},
+                                            {4, 1, 4, 3, {0.476, 0.780, 1.200}, 5.1},
+                                            {2, 1, 4, 4, {0.305, 0.527, 0.816, 1.121}, 4.2}};
 
-double step_cost(const TileCost& c, int64_t per_cu) {
-    return per_cu <= 1 ? c.step1 : per_cu == 2 ? c.step2 : c.step3;
-}
+int row_tiles(int M, const TileCost& c) { return (M + c.bm() - 1) / c.bm(); }
+int col_tiles(int N, const TileCost& c) { return (N + c.bn() - 1) / c.bn(); }
 
 double launch_cost(int64_t wgs, int nsteps, const TileCost& c, int P) {
     if (wgs <= 0) return 0.0;
     const int64_t slots = (int64_t)c.occ * P;
     const int64_t full = wgs / slots, rem = wgs % slots;
-    return c.fixed + (double)full * nsteps * step_cost(c, c.occ) +
-           (rem == 0 ? 0.0 : nsteps * step_cost(c, (rem + P - 1) / P));
+    return c.fixed + (double)full * nsteps * c.step[c.occ - 1] + (rem == 0 ? 0.0 : nsteps * c.step[(rem + P - 1) / P - 1]);
 }
 
-struct Launch {
-    int row0, row1, bm, tn;
-};
 struct Plan {
-    int n;       // launches
-    int splits;  // k-splits of a single launch (1: none)
-    Launch l[2];
+    int tile;    // index into kTileCosts
+    int splits;  // k-splits (1: none)
 };
-// k-split: the GEMM writes one binary32 partial output per split (≈ 5 TB/s, on top of its
-// k-steps), and one extra launch reads them back and writes the output (measured ≈ 7 TB/s:
-// the partials come back from the last-level cache in part)
-double reduce_cost(int64_t M, int64_t N, int splits) {
-    return splits > 1 ? 2.0 + (double)(splits + 1) * (double)(M * N * 4) / 7.0e6 +
-                            (double)splits * (double)(M * N * 4) / 5.0e6
-                      : 0.0;
+// The output write: 6.3 TB/s non-temporally.  k-split: one partial output per split, written
+// (5.3 TB/s) and read back with the final write by one extra launch (11 TB/s: the partials come
+// from the last-level cache in part), which costs 5 us itself.
+double output_cost(int64_t M, int64_t N, int splits) {
+    const double mb = (double)(M * N * 4) * 1e-6;
+    return splits > 1 ? 5.03 + 0.187 * splits * mb + 0.089 * (splits + 1) * mb : 0.158 * mb;
 }
 
-int col_tiles(int N, int tn) { return (N + tile_width(tn) - 1) / tile_width(tn); }
-
-Plan plan_gemm(int M, int N, int K, int code_bits) {
+Plan plan_gemm(int M, int N, int K) {
     const int P = cu_count();
     const int nsteps = K / BK;
-    TileCost costs[kNumTiles];
-    for (int b = 0; b < kNumTiles; ++b) costs[b] = kTileCosts[b];
-    if (code_bits != 4) {  // the full-width 128-high tile with 8-bit codes: one per CU
-        costs[1].occ = 1;
-        costs[1].step2 = costs[1].step3 = costs[1].step1;
-    }
-    // half-width tiles: with 4-bit codes wherever the model prefers them; with 8-bit codes
-    // (the costs are fitted on 4-bit codes) only where the full-width tiles leave CUs idle
-    const bool half_ok = code_bits == 4 || (int64_t)((M + 127) / 128) * col_tiles(N, 2) < P;
-    // 64 x 128 tiles (three per CU), outside the model: for short 4-bit layers whose
-    // 128 x 128 tiles fill at most half the CUs and whose 64 x 128 tiles fill at least half,
-    // they beat every plan the model offers (1024 x 1280 x 1280: 12.5 us against 18.3 us for
-    // 3 k-splits of 128 x 128 tiles); on the shapes measured outside that range they lost
-    const int64_t t128 = (int64_t)((M + 127) / 128) * col_tiles(N, 1), t64 = (int64_t)((M + 63) / 64) * col_tiles(N, 1);
-    if (code_bits == 4 && nsteps <= 20 && 2 * t128 <= P && 2 * t64 >= P)
-        return Plan{1, 1, {Launch{0, M, 64, 1}, Launch{0, 0, 0, 0}}};
     double best = 1e300;
-    Plan plan{1, 1, {Launch{0, M, 64, 2}, Launch{0, 0, 0, 0}}};
+    Plan plan{0, 1};
     for (int b = 0; b < kNumTiles; ++b) {
-        if (costs[b].tn == 1 && !half_ok) continue;
-        const int tn = col_tiles(N, costs[b].tn);
+        const TileCost& c = kTileCosts[b];
+        const int64_t tiles = (int64_t)row_tiles(M, c) * col_tiles(N, c);
         for (int sp = 1; sp <= kMaxSplits && sp <= nsteps; ++sp) {
             const int kchunk = (nsteps + sp - 1) / sp;
             if (sp > 1 && (sp - 1) * kchunk >= nsteps) continue;  // an empty split
-            const int64_t tiles = (int64_t)((M + costs[b].bm - 1) / costs[b].bm) * tn;
-            const double c = launch_cost(tiles * sp, kchunk, costs[b], P) + reduce_cost(M, N, sp);
-            if (c < best) { best = c; plan = Plan{1, sp, {Launch{0, M, costs[b].bm, costs[b].tn}, Launch{0, 0, 0, 0}}}; }
-        }
-    }
-    // one tile shape for whole rounds of full tile rows, another for the rows left
-    for (int b = 0; b < kNumTiles; ++b) {
-        if (costs[b].tn == 1 && !half_ok) continue;
-        const TileCost& c1 = costs[b];
-        const int tn1 = col_tiles(N, c1.tn);
-        const int rows_per_round = (c1.occ * P / tn1) * c1.bm;
-        if (rows_per_round <= 0) continue;
-        const int r1 = (M / rows_per_round) * rows_per_round;
-        if (r1 <= 0 || r1 >= M) continue;
-        for (int b2 = 0; b2 < kNumTiles; ++b2) {
-            if (b2 == b || (costs[b2].tn == 1 && !half_ok)) continue;
-            const TileCost& c2 = costs[b2];
-            const double c = launch_cost((int64_t)(r1 / c1.bm) * tn1, nsteps, c1, P) +
-                             launch_cost((int64_t)((M - r1 + c2.bm - 1) / c2.bm) * col_tiles(N, c2.tn), nsteps, c2, P);
-            if (c < best) { best = c; plan = Plan{2, 1, {Launch{0, r1, c1.bm, c1.tn}, Launch{r1, M, c2.bm, c2.tn}}}; }
+            const double t = launch_cost(tiles * sp, kchunk, c, P) + output_cost(M, N, sp);
+            if (t < best) { best = t; plan = Plan{b, sp}; }
         }
     }
     return plan;
 }
 
-// partial-output bytes of the plan for these sizes (the larger of the two code widths)
+// partial-output bytes of the plan for these sizes
 size_t split_bytes(int64_t M, int64_t N, int64_t K) {
-    size_t b = 0;
-    for (int bits = 4; bits <= 8; bits += 4) {
-        const Plan p = plan_gemm((int)M, (int)N, (int)K, bits);
-        if (p.splits > 1) b = std::max(b, (size_t)p.splits * (size_t)M * (size_t)N * 4);
+    const Plan p = plan_gemm((int)M, (int)N, (int)K);
+    return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * 4 : 0;
+}
+
+template <int AF>
+void launch_gemm_af(const GemmArgs& a, int tile, unsigned grid, hipStream_t s) {
+    switch (tile) {
+    case 0: hipLaunchKernelGGL((gemm_kernel<4, 2, 4, AF>), dim3(grid), dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((gemm_kernel<4, 1, 4, AF>), dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((gemm_kernel<2, 1, 4, AF>), dim3(grid), dim3(256), 0, s, a); break;
     }
-    return b;
 }
 
-template <int CODE_BITS, int AF>
-void launch_gemm_af(const GemmArgs& a, const Launch& l, hipStream_t s) {
-    const unsigned grid = (unsigned)(((l.row1 - l.row0 + l.bm - 1) / l.bm) * a.tn * a.splits);
-    if (l.bm == 256) hipLaunchKernelGGL((gemm_kernel<CODE_BITS, 8, AF, 2>), dim3(grid), dim3(kThreads), 0, s, a);
-    else if (l.bm == 128 && l.tn == 1)
-        hipLaunchKernelGGL((gemm_kernel<CODE_BITS, 4, AF, 1>), dim3(grid), dim3(kThreads), 0, s, a);
-    else if (l.bm == 128) hipLaunchKernelGGL((gemm_kernel<CODE_BITS, 4, AF, 2>), dim3(grid), dim3(kThreads), 0, s, a);
-    else if (l.tn == 1) hipLaunchKernelGGL((gemm_kernel<CODE_BITS, 2, AF, 1>), dim3(grid), dim3(kThreads), 0, s, a);
-    else hipLaunchKernelGGL((gemm_kernel<CODE_BITS, 2, AF, 2>), dim3(grid), dim3(kThreads), 0, s, a);
-}
+// Tile rows per group of the XCD-aware order, 0 for the row-major one.  What decides is the
+// order in which the output lines reach memory: with larger groups (8 - 16 rows, which read the
+// fewest operand bytes) the tiles written at one time lie in many rows and a few columns, and a
+// cold 8192 x 5120 x 640 took 78 - 93 us against 61 - 66 in groups of two rows; 8192 x 640 x 2560
+// 44.4 against 37.3.  Row-major puts workgroup b on XCD b % 8 and tile column b % tn: where tn
+// is a multiple of 8 each XCD keeps the same eighth of the weights in its L2 and whole rows are
+// written at one time (2048 x 10240 x 1280, cold: 57.6 us against 70.0 in groups of two;
+// 1024 x 10240 x 1280: 32.7 against 42.2), elsewhere every XCD walks all weights and it loses
+// (8192 x 3456 x 1152: 85.5 against 72.4).
+int group_rows(int mt, int tn) { return tn % 8 == 0 && tn >= 32 ? 0 : std::min(2, mt); }
 
-// Tile rows per group of the XCD-aware order, or 0 for row-major order.  The XCD-aware
-// order is taken where a workgroup runs at least 24 k-steps: there one tile's operand slabs
-// are large enough that the row-major order's share of an XCD (most tile rows, several
-// columns) overflows its L2; measured on the sweep stack's FF-out layers, 3-5 % faster,
-// while the shorter layers ran 2-4 % slower in it.  An XCD's block of tiles (T of them,
-// about r rows by T / r columns) reads r activation row tiles and T / r weight column
-// tiles, so r = sqrt(T x column-tile bytes / row-tile bytes) reads the least; the divisor
-// of the tile rows nearest to it (in ratio) keeps the groups whole.
-int group_rows(int mt, int tn, int splits, int kchunk, int bm, int bn, bool half_act, int code_bits) {
-    if (kchunk < 24) return 0;
-    const double T = std::ceil((double)mt * tn * splits / 8.0);
-    const double row_bytes = (double)bm * (half_act ? 2.0 : 1.0);
-    const double col_bytes = (double)bn * (code_bits == 4 ? 1.5 : 2.0);
-    const double r = std::sqrt(T * col_bytes / row_bytes);
-    int best = 1;
-    for (int d = 1; d <= mt; ++d)
-        if (mt % d == 0 && std::fabs(std::log((double)d / r)) < std::fabs(std::log((double)best / r))) best = d;
-    return best;
-}
-
-template <int CODE_BITS>
-void launch_gemm(GemmArgs a, const Launch& l, int af, hipStream_t s) {
-    a.row0 = l.row0;
-    a.row1 = l.row1;
-    a.tn = col_tiles(a.N, l.tn);
-    a.gm = group_rows((l.row1 - l.row0 + l.bm - 1) / l.bm, a.tn, a.splits, a.kchunk, l.bm, tile_width(l.tn),
-                      af == kAF16 || af == kAConv, CODE_BITS);
+void launch_gemm(GemmArgs a, int tile, int af, hipStream_t s) {
+    const TileCost& c = kTileCosts[tile];
+    const int mt = row_tiles(a.M, c);
+    a.tn = col_tiles(a.N, c);
+    a.gm = group_rows(mt, a.tn);
+    a.cached = a.splits > 1 || (a.N & 31) != 0;
+    const unsigned grid = (unsigned)(mt * a.tn * a.splits);
     switch (af) {
-    case kAInt8: launch_gemm_af<CODE_BITS, kAInt8>(a, l, s); break;
-    case kAE4M3: launch_gemm_af<CODE_BITS, kAE4M3>(a, l, s); break;
-    case kAE5M2: launch_gemm_af<CODE_BITS, kAE5M2>(a, l, s); break;
-    case kAConv: launch_gemm_af<CODE_BITS, kAConv>(a, l, s); break;
-    default: launch_gemm_af<CODE_BITS, kAF16>(a, l, s); break;
+    case kAInt8: launch_gemm_af<kAInt8>(a, tile, grid, s); break;
+    case kAE4M3: launch_gemm_af<kAE4M3>(a, tile, grid, s); break;
+    case kAE5M2: launch_gemm_af<kAE5M2>(a, tile, grid, s); break;
+    case kAConv: launch_gemm_af<kAConv>(a, tile, grid, s); break;
+    default: launch_gemm_af<kAF16>(a, tile, grid, s); break;
     }
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
-// weight record slots (48 or 64 bytes used) per (k-step, channel, half)
-int64_t record_bytes(int64_t N, int64_t K) { return N * (K / BK) * 2 * 64; }
+// half-precision weights: whole blocks of 32 channels
+int64_t weight_bytes(int64_t N, int64_t K) { return (N + 31) / 32 * (K / BK) * (kBlockChunks * 16); }
 
 }  // namespace
 }  // namespace cham
@@ -1154,13 +1030,13 @@ extern "C" size_t cham_packed_bytes(int64_t N, int64_t K) {
     if (N < 1 || K < 64) return 0;
     int nkc, rchunk;
     rec_chunks(N, K, &nkc, &rchunk);
-    return align256((size_t)N * sizeof(ColPrep)) + align256((size_t)nkc * (size_t)N * 4) + (size_t)record_bytes(N, K);
+    return align256((size_t)N * sizeof(ColPrep)) + align256((size_t)nkc * (size_t)N * 4) + (size_t)weight_bytes(N, K);
 }
 
 struct Layout {
     ColPrep* cols;
     float* colsum;
-    uint4* rec;
+    uint4* wh;
 };
 static Layout layout_at(void* p, int64_t N, int64_t K) {
     int nkc, rchunk;
@@ -1171,7 +1047,7 @@ static Layout layout_at(void* p, int64_t N, int64_t K) {
     c += align256((size_t)N * sizeof(ColPrep));
     l.colsum = (float*)c;
     c += align256((size_t)nkc * (size_t)N * 4);
-    l.rec = (uint4*)c;
+    l.wh = (uint4*)c;
     return l;
 }
 
@@ -1216,7 +1092,7 @@ static RecArgs record_args(const WView& v, const Layout& L, int* wgs) {
     *wgs = nblk * nkc;
     // block metadata only of the enabled formats (the pre-pass reads it ahead of the format)
     return RecArgs{v.fmt, v.scale, v.zero, nf4 && !v.gsel ? v.nf4 : nullptr, wmx ? v.e8 : nullptr, v.codes,
-                   mask, N, K, v.code_bits, rchunk, L.cols, L.colsum, L.rec, v.gsel, v.gscale, v.gzero};
+                   mask, N, K, v.code_bits, rchunk, L.cols, L.colsum, L.wh, v.gsel, v.gscale, v.gzero};
 }
 
 static void launch_records(const WView& v, const Layout& L, hipStream_t s) {
@@ -1293,16 +1169,13 @@ extern "C" int cham_linear_plan(int64_t M, int64_t N, int64_t K, int32_t code_bi
     if (!out || out_len < 10 || M < 1 || N < 1 || K < 1 || M > INT32_MAX || N > INT32_MAX || K > INT32_MAX ||
         (code_bits != 4 && code_bits != 8))
         return CHAM_EINVAL;
-    const Plan p = plan_gemm((int)M, (int)N, (int)K, code_bits);
+    const Plan p = plan_gemm((int)M, (int)N, (int)K);
     for (int i = 0; i < 10; ++i) out[i] = 0;
-    out[0] = p.n;
+    out[0] = 1;
     out[1] = p.splits;
-    for (int i = 0; i < p.n; ++i) {
-        out[2 + 4 * i] = p.l[i].row0;
-        out[3 + 4 * i] = p.l[i].row1;
-        out[4 + 4 * i] = p.l[i].bm;
-        out[5 + 4 * i] = tile_width(p.l[i].tn);
-    }
+    out[3] = (int32_t)M;
+    out[4] = kTileCosts[p.tile].bm();
+    out[5] = kTileCosts[p.tile].bn();
     return CHAM_OK;
 }
 
@@ -1365,7 +1238,7 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
     // 32-bit buffer offsets: a 256-row activation tile, a 256-row output tile and the
     // weight records stay below 2^31 bytes
     if (xq->M > INT32_MAX / 2 || wq->N > INT32_MAX / 1024 || wq->K > (1 << 20) ||
-        record_bytes(wq->N, wq->K) > (int64_t)INT32_MAX)
+        wq->N * (wq->K / BK) * 128 > (int64_t)INT32_MAX)
         return CHAM_ESHAPE;
     const bool nf4 = (mask >> CHAM_W_NF4) & 1u;
     const bool wmx = (mask & ((1u << CHAM_W_MXINT8) | (1u << CHAM_W_MXINT4) | (1u << CHAM_W_MXFP4))) != 0u;
@@ -1375,7 +1248,7 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
     if (((uintptr_t)xq->codes & 15u) || ((uintptr_t)wq->codes & 15u) || ((uintptr_t)wq->packed & 255u))
         return CHAM_EINVAL;
     const int M = (int)xq->M, N = (int)wq->N, K = (int)wq->K;
-    const Plan plan = plan_gemm(M, N, K, code_bits);
+    const Plan plan = plan_gemm(M, N, K);
     const int kchunk = (K / BK + plan.splits - 1) / plan.splits;
     // every split holds at least one k-step (the operand ranges of the kernel rely on it)
     if (plan.splits < 1 || (plan.splits - 1) * kchunk >= K / BK) return CHAM_ESHAPE;
@@ -1401,12 +1274,12 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
             hipLaunchKernelGGL(emax_kernel, dim3(1), dim3(1024), 0, s, xq->e8m0, xq->M * (xq->K / 32), emax);
             CHAM_CHECK_LAUNCH();
         }
-        PrepConvArgs p{xq->codes, xq->e8m0, xq->fmt, cv->B, cv->H, cv->W, (int)xq->K, code_bits == 4, xq->scale,
+        PrepConvArgs p{xq->codes, xq->e8m0, xq->fmt, cv->B, cv->H, cv->W, (int)xq->K, xq->scale,
                        xq->zero, (int)(xq->M / xq->nsamples), emax, Xh, rowscale};
         hipLaunchKernelGGL(prep_conv_kernel, dim3((unsigned)(cv->B * (cv->H + 2) * (cv->W + 2))), dim3(256), 0, s, p);
         CHAM_CHECK_LAUNCH();
     } else if (amx) {
-        PrepArgs p{xq->codes, xq->e8m0, xq->fmt, M, K, code_bits == 4, Xh, rowscale};
+        PrepArgs p{xq->codes, xq->e8m0, xq->fmt, M, K, Xh, rowscale};
         hipLaunchKernelGGL(prep_kernel, dim3((unsigned)M), dim3(256), 0, s, p);
         CHAM_CHECK_LAUNCH();
     }
@@ -1427,13 +1300,11 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
         int rchunk;
         rec_chunks(N, K, &a.nkc, &rchunk);
     }
-    a.rec = lay.rec;
+    a.wh = lay.wh;
     a.Y = Y;
     a.M = M;
     a.N = N;
     a.K = K;
-    a.row0 = 0;
-    a.row1 = M;
     a.part = part;
     a.H = cv ? cv->H : 0;
     a.W = cv ? cv->W : 0;
@@ -1444,11 +1315,8 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
                        : (xq->fmt == CHAM_A_INT8_ASYM ? kAInt8 : (xq->fmt == CHAM_A_FP8_E4M3 ? kAE4M3 : kAE5M2));
     a.splits = plan.splits;
     a.kchunk = kchunk;
-    for (int i = 0; i < plan.n; ++i) {
-        if (code_bits == 4) launch_gemm<4>(a, plan.l[i], af, s);
-        else launch_gemm<8>(a, plan.l[i], af, s);
-        CHAM_CHECK_LAUNCH();
-    }
+    launch_gemm(a, plan.tile, af, s);
+    CHAM_CHECK_LAUNCH();
     if (plan.splits > 1) {
         const int64_t MN = (int64_t)M * N;
         const int64_t per = (MN & 3) == 0 ? MN / 4 : MN;

@@ -1,11 +1,15 @@
-// GEMM-ready layout of a searched weight ("records"), written by the record pre-pass (into
-// the weight's packed buffer when the search asks for it, else into the linear layer's
-// workspace) and read by the GEMM: per output channel a ColPrep, and per
-// (k-step of 64, channel, half k-step of 32) a record of the half's codes followed by a
-// 16-entry half-precision decode table (base value x block factor relative to the channel's
-// largest block, rounded to binary32 and then to half precision) as two byte planes; and per
-// channel the sum of its dequantized weights (the zero-point correction of INT8-asym
-// activations whose zero point lies beyond what the half-precision decode holds exactly).
+// GEMM-ready layout of a searched weight, written by the packing pass (into the weight's
+// packed buffer when the search asks for it, else into the linear layer's workspace) and read
+// by the GEMM: per output channel a ColPrep; per channel the sum of its dequantized weights
+// (the zero-point correction of INT8-asym activations whose zero point lies beyond what the
+// half-precision decode holds exactly), in partials over chunks of k; and the weights in half
+// precision relative to the channel's scale, as the MFMA operand wants them: per (k-step of 64,
+// block of 32 channels) 256 chunks of 16 bytes, chunk (s, h, c) = the 8 weights of channel c at
+// k = 32 h + 8 s (1 KB per sub-step s, consecutive over the 64 lanes).  The last block's missing
+// channels are not written.  The tables below are how the packing pass decodes a record, the 32
+// codes of a (k-step, channel, half h): 16 half-precision entries (base value x block factor
+// relative to the channel's largest block, rounded to binary32 and then to half precision) as
+// two byte planes.
 #ifndef CHAM_RECORDS_H_
 #define CHAM_RECORDS_H_
 
