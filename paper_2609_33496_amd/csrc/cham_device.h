@@ -173,6 +173,68 @@ CHAM_DEV float group_max(float v) {
 }
 
 // ------------------------------------------------------------------------------------
+// DPP moves within a wavefront row
+// ------------------------------------------------------------------------------------
+// Every control used here reads a lane of the same wavefront row, so no lane is invalid and
+// bound_ctrl is free to set: it lets the compiler fold the move into the consuming min/max/add.
+template <int CTRL>
+CHAM_DEV float dpp(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// ------------------------------------------------------------------------------------
+// NF4 lookup: cell i of [-1, 1] (width 1/16) holds cnt = number of decision thresholds
+// below the cell's lower bound, the first threshold at or above it (+inf if none), and
+// the levels cnt and cnt+1.  Consecutive thresholds are more than 1/16 apart and none is
+// within 1e-3 of a cell boundary, so for y in the cell the nearest level is
+// cnt + (y > thr); an index computed one cell off near a boundary gives the same code.
+// ------------------------------------------------------------------------------------
+struct NF4Cell {
+    float thr, vlo, vhi;
+    uint32_t cnt;
+};
+
+// filled by the workgroup's first 33 threads
+CHAM_DEV void nf4_cells_init(NF4Cell* cells) {
+    const int i = threadIdx.x;
+    if (i < 33) {
+        const float b = -1.0f + (float)i * 0.0625f;
+        uint32_t cnt = 0;
+#pragma unroll
+        for (int j = 0; j < 15; ++j) cnt += (__uint_as_float(kNF4ThrBits[j]) < b) ? 1u : 0u;
+        NF4Cell c;
+        c.cnt = cnt;
+        c.thr = cnt < 15 ? __uint_as_float(kNF4ThrBits[cnt]) : INFINITY;
+        c.vlo = nf4_level(cnt);
+        c.vhi = nf4_level(cnt < 15 ? cnt + 1 : 15);
+        cells[i] = c;
+    }
+}
+
+// y = w fl(1/a) with |w| <= a, so |y| <= 1 + 2^-23: 16 y + 16 truncates to 0 .. 32.
+CHAM_DEV NF4Cell nf4_cell(const NF4Cell* cells, float y) {
+    return cells[(int)__builtin_fmaf(y, 16.0f, 16.0f)];
+}
+
+// ------------------------------------------------------------------------------------
+// FP4 round trip by the hardware converters
+// ------------------------------------------------------------------------------------
+typedef float v2f __attribute__((ext_vector_type(2)));
+
+// 2^E as the binary32 scale operand of the FP4 converters (they read its exponent field)
+CHAM_DEV float e8m0_scale(int E) { return __uint_as_float((uint32_t)(E + 127) << 23); }
+
+// E2M1 round trip of four values through the hardware converter with a power-of-two scale:
+// the two pairs' codes go to bytes 0 and 1 of one register.  `old` is any value that is
+// dead after the call (the converter only replaces the selected byte).
+CHAM_DEV void fp4_quad(float y0, float y1, float y2, float y3, float scale, uint32_t old, v2f& lo, v2f& hi) {
+    uint32_t c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(old, y0, y1, scale, 0);
+    c = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(c, y2, y3, scale, 1);
+    lo = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, scale, 0);
+    hi = __builtin_amdgcn_cvt_scalef32_pk_f32_fp4(c, scale, 1);
+}
+
+// ------------------------------------------------------------------------------------
 // activation codes of one float4 (App. A.11; the quantize pass and the fused
 // quantize-and-accumulate pass share this arithmetic, so their codes are the same bits)
 // ------------------------------------------------------------------------------------

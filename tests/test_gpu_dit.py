@@ -143,6 +143,35 @@ def test_colsq_accumulate():
     assert np.allclose(_np(colsq), ref, rtol=1e-12, atol=0)
 
 
+@pytest.mark.parametrize("mask", [cham.MASK_DIT_W4, 0x1FF])
+@pytest.mark.parametrize("N,K", [(1, 32), (5, 288), (4, 608), (2, 7904)])
+def test_group_search_edges(mask, N, K):
+    """One block, whole and short last groups of every size, rows of one and of several
+    staging passes; groups that are zero, constant, one-sided, subnormal and large
+    (+-1e38: the range hi - lo must stay finite, or the INT-asym errors are NaN by definition)."""
+    W, _ = synth.hetero_weights(3 * N + K, N, K)
+    W[0, :32] = 0.0
+    for b, v in enumerate((W[-1, 32:64] * 0 + np.float32(0.37), np.abs(W[0, :32]) + np.float32(2.0),
+                           W[0, 32:64] * np.float32(1e-39), np.sign(W[-1, :32]) * np.float32(1e38))):
+        k = 32 * (b + 1)
+        if k + 32 <= K:
+            W[N // 2, k:k + 32] = v if v.size else 0.0
+    e = np.exp(np.random.default_rng(K).normal(0, 1, K)).astype(np.float32)
+    for gmask in (cham.GMASK_ALL, 0b10001):
+        gq, ref = _gsearch_both(W, e, mask, gmask)
+        _assert_gsearch_equal(gq, ref)
+
+
+@pytest.mark.parametrize("M,K", [(1, 1), (63, 65), (130, 1000), (2100, 63)])
+def test_colsq_edges(M, K):
+    """Fewer rows than chunks, rows left over from the unrolled ones, partial channel blocks."""
+    X = np.random.default_rng(M + K).standard_normal((M, K)).astype(np.float32)
+    colsq = torch.full((K,), 2.0, dtype=torch.float64, device=DEV)
+    case(f"act_colsq_accumulate M={M} K={K}")
+    cham.act_colsq_accumulate(torch.from_numpy(X).to(DEV), colsq)
+    assert np.allclose(_np(colsq), 2.0 + np.sum(X.astype(np.float64) ** 2, axis=0), rtol=1e-12, atol=0)
+
+
 @pytest.mark.parametrize("mask", [cham.MASK_DIT_W4, cham.MASK_W8])
 def test_group_search_pixart_layers_and_gemm(mask):
     """PixArt-like proj (1152 -> 1152) and cross-attention KV (4096 -> 1152: K not a
