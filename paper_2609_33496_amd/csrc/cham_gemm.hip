@@ -14,9 +14,12 @@
 // 65.2 us on 2048 x 10240 x 1280 (now 55.8) and, with 8-bit codes, 153 us on
 // 8192 x 4608 x 1152 (now 87).
 //
-// Activations in a per-tensor format (INT8, E4M3, E5M2) are decoded to half precision
-// while they are staged into LDS (exact); MX activations are decoded by a pre-pass into a
-// half-precision copy relative to the row's largest block exponent, with a row scale.
+// Activations are decoded to half precision while they are staged into LDS: per-tensor formats
+// (INT8, E4M3, E5M2) exactly, MX formats relative to the largest block exponent of the row
+// (3x3 convolution: of the pixels the tile gathers), which each workgroup finds in the
+// exponent bytes first.  That adds 3 us to the MXFP8 product 8100 x 640 x 1920 (29.9 -> 32.9)
+// and 5 to the convolution 1920 -> 640 at 2 x 32 x 32 (49.8 -> 54.9); the pre-passes that wrote
+// a half-precision copy instead took 13.7 and 38.8 us.
 //
 // Main kernel: 128 x 256, 128 x 128 or 64 x 128 output tiles; k-steps of 64; four wavefronts
 // side by side that each own all the tile's rows x 32 TN channels (blocks of
@@ -58,130 +61,6 @@ constexpr int tile_width(int TN, int NW) { return 32 * TN * NW; }
 constexpr int kBlockChunks = 256;
 constexpr int kBufferFlags = 0x00020000;  // buffer descriptor word 3: 32-bit data, raw
 constexpr int kStoreNonTemporal = 2;      // cache-policy operand of a buffer store: nt
-
-// ------------------------------------------------------------------------------------
-// pre-pass for MX activation formats: codes -> half precision relative to the row's
-// largest block exponent (exact for blocks within 2^28 of it), the row scale separately
-// ------------------------------------------------------------------------------------
-struct PrepArgs {
-    const uint8_t* xc;
-    const uint8_t* xe8;
-    int afmt;
-    int M, K;
-    _Float16* Xh;
-    float* rowscale;
-};
-
-// One workgroup per activation row.
-__global__ __launch_bounds__(256) void prep_kernel(PrepArgs p) {
-    const int K = p.K;
-    const int m = blockIdx.x;
-    __shared__ int sh_e;
-    int mx_e = 0;
-    for (int b = threadIdx.x; b < K / 32; b += blockDim.x) mx_e = max(mx_e, (int)p.xe8[(int64_t)m * (K / 32) + b]);
-    for (int o = 32; o > 0; o >>= 1) mx_e = max(mx_e, __shfl_xor(mx_e, o, kWave));
-    if (threadIdx.x == 0) sh_e = 0;
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) atomicMax(&sh_e, mx_e);
-    __syncthreads();
-    // the row's largest block lands at [2^14, 2^15): blocks down to 2^-28 of it stay normal
-    // in half precision (values are below 2 times 2^(block exponent - eref))
-    const int eref = sh_e - 127 - 14;
-    const uint8_t* row = p.xc + (int64_t)m * K;
-    _Float16* out = p.Xh + (int64_t)m * K;
-    for (int g = threadIdx.x; g < K / 8; g += blockDim.x) {
-        const uint2 c2 = *reinterpret_cast<const uint2*>(row + 8 * g);
-        const int kb = (int)p.xe8[(int64_t)m * (K / 32) + (g >> 2)] - 127;
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t c = ((j < 4 ? c2.x : c2.y) >> (8 * (j & 3))) & 0xFFu;
-            v[j] = p.afmt == CHAM_A_MXFP8_E4M3 ? ldexpf(e4m3_decode(c), kb - eref)
-                                               : ldexpf((float)(int8_t)c, kb - 6 - eref);
-        }
-        half8 h;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
-        *reinterpret_cast<half8*>(out + 8 * g) = h;
-    }
-    if (threadIdx.x == 0) p.rowscale[m] = ldexpf(1.0f, eref);
-}
-
-// ------------------------------------------------------------------------------------
-// pre-pass of the 3x3 convolution: the activation codes -> a zero-padded half-precision
-// copy [B][H+2][W+2][C] (the border is the padding) that the GEMM gathers per output pixel
-// and tap.  MX formats relative to the tensor's largest block exponent (every output row
-// gathers nine pixels, so they need one reference), per-tensor formats as code values
-// (E4M3, E5M2 exact) or q - z (INT8-asym) with the sample's scale as the row scale.
-// ------------------------------------------------------------------------------------
-struct PrepConvArgs {
-    const uint8_t* xc;
-    const uint8_t* xe8;
-    int afmt;
-    int B, H, W, C;
-    const float* xs;  // per-sample scale / zero point (per-tensor formats)
-    const float* xz;
-    int rps;          // rows (pixels) per sample
-    int* emax;        // MX: the largest biased block exponent of the tensor (device)
-    _Float16* Xh;
-    float* rowscale;  // [B*H*W]
-};
-
-// One workgroup: the largest E8M0 byte of n (a plain maximum, so the order is free).
-__global__ __launch_bounds__(1024) void emax_kernel(const uint8_t* e8, int64_t n, int* out) {
-    int m = 0;
-    for (int64_t i = threadIdx.x; i < n; i += 1024) m = max(m, (int)e8[i]);
-    for (int o = 32; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o, kWave));
-    __shared__ int wm[16];
-    if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 16; ++i) m = max(m, wm[i]);
-        *out = max(m, wm[0]);
-    }
-}
-
-// One workgroup per padded pixel.
-__global__ __launch_bounds__(256) void prep_conv_kernel(PrepConvArgs p) {
-    const int C = p.C, Wp = p.W + 2, Hp = p.H + 2;
-    const int pp = blockIdx.x, xp = pp % Wp, yb = pp / Wp, yp = yb % Hp, b = yb / Hp;
-    _Float16* out = p.Xh + (int64_t)pp * C;
-    const bool border = xp == 0 || yp == 0 || xp == Wp - 1 || yp == Hp - 1;
-    if (border) {
-        for (int g = threadIdx.x; g < C / 8; g += blockDim.x) *reinterpret_cast<uint4*>(out + 8 * g) = make_uint4(0u, 0u, 0u, 0u);
-        return;
-    }
-    const int64_t m = ((int64_t)b * p.H + (yp - 1)) * p.W + (xp - 1);  // source = output row
-    const bool mx = p.afmt == CHAM_A_MXFP8_E4M3 || p.afmt == CHAM_A_MXINT8;
-    const float z = mx ? 0.0f : p.xz[m / p.rps];
-    // MX: the tensor's reference exponent; INT8-asym: the power of two that keeps q - z
-    // within half precision's range
-    const float zm = fabsf(z) + 255.0f;
-    const int eref = mx ? *p.emax - 127 - 14
-                        : (p.afmt == CHAM_A_INT8_ASYM && zm >= 32768.0f ? floor_log2(zm) - 14 : 0);
-    const uint8_t* row = p.xc + m * C;
-    for (int g = threadIdx.x; g < C / 8; g += blockDim.x) {
-        const uint2 c2 = *reinterpret_cast<const uint2*>(row + 8 * g);
-        const int kb = mx ? (int)p.xe8[m * (C / 32) + (g >> 2)] - 127 : 0;
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t c = ((j < 4 ? c2.x : c2.y) >> (8 * (j & 3))) & 0xFFu;
-            switch (p.afmt) {
-            case CHAM_A_MXFP8_E4M3: v[j] = ldexpf(e4m3_decode(c), kb - eref); break;
-            case CHAM_A_MXINT8: v[j] = ldexpf((float)(int8_t)c, kb - 6 - eref); break;
-            case CHAM_A_FP8_E4M3: v[j] = e4m3_decode(c); break;
-            case CHAM_A_FP8_E5M2: v[j] = e5m2_decode(c); break;
-            default: v[j] = ldexpf((float)c - z, -eref); break;  // INT8-asym
-            }
-        }
-        half8 h;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) h[j] = (_Float16)v[j];
-        *reinterpret_cast<half8*>(out + 8 * g) = h;
-    }
-    if (threadIdx.x == 0) p.rowscale[m] = mx ? ldexpf(1.0f, eref) : ldexpf(p.xs[m / p.rps], eref);
-}
 
 // ------------------------------------------------------------------------------------
 // weight decode
@@ -498,9 +377,8 @@ CHAM_DEV void lds_barrier() {
 // main kernel
 // ------------------------------------------------------------------------------------
 struct GemmArgs {
-    const _Float16* Xh;      // [M][K], MX activation formats
-    const float* rowscale;   // [M], MX activation formats
-    const uint8_t* xc;       // [M][K] activation codes, per-tensor formats
+    const uint8_t* xc;       // [M][K] activation codes
+    const uint8_t* xe8;      // [M][K/32] block exponents, MX activation formats
     const float* xs;         // activation scale per sample [M / rps] (per-tensor formats)
     const float* xz;         // activation zero point per sample
     int rps;                 // rows per sample
@@ -516,57 +394,123 @@ struct GemmArgs {
     int splits;      // k-splits: workgroup b takes tile b % tiles and k-steps of split b / tiles
     int kchunk;      // k-steps per split
     float* part;     // splits > 1: [splits][M][N] partial outputs, summed by reduce_kernel
-    // 3x3 convolution (implicit GEMM): Xh is the zero-padded activation [B][H+2][W+2][C] in
-    // half precision; row m = (b, y, x) of the output, k = (ky * 3 + kx) * C + c
+    // 3x3 convolution (implicit GEMM): xc is [B][H][W][C]; row m = (b, y, x) of the output,
+    // k = (ky * 3 + kx) * C + c gathers pixel (y + ky - 1, x + kx - 1), zero past the borders
     int H, W, C;
-    uint32_t xh_bytes;
 };
 
-// Activation operand source: the half-precision copy of the pre-pass (MX formats), the
-// per-tensor codes, decoded while they are staged into LDS, or (3x3 convolution) the
-// pre-pass's zero-padded half-precision copy, gathered per output pixel and tap.
-constexpr int kAF16 = 0, kAInt8 = 1, kAE4M3 = 2, kAE5M2 = 3, kAConv = 4;
+CHAM_DEV constexpr bool mx_act(int af) { return af == CHAM_A_MXFP8_E4M3 || af == CHAM_A_MXINT8; }
 
-// 8 activation codes (k0..k3 in w0, k4..k7 in w1) -> 8 halves in that order; exact for all
-// three per-tensor formats.
+// INT8-asym convolution: the power of two 2^-eref that keeps q - z within half precision's range
+CHAM_DEV int far_eref(float z) {
+    const float zm = fabsf(z) + 255.0f;
+    return zm >= 32768.0f ? floor_log2(zm) - 14 : 0;
+}
+
+// largest of the bytes p[o0 .. o1), at most 16 (any alignment)
+CHAM_DEV int max_bytes(const uint8_t* p, int o0, int o1) {
+    int m = 0;
+    if (o1 - o0 == 16) {
+        uint32_t w[4];
+        __builtin_memcpy(w, p + o0, 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            m = max(m, max(max((int)(w[i] & 0xFFu), (int)((w[i] >> 8) & 0xFFu)), max((int)((w[i] >> 16) & 0xFFu), (int)(w[i] >> 24))));
+    } else {
+        for (int o = o0; o < o1; ++o) m = max(m, (int)p[o]);
+    }
+    return m;
+}
+
+// What a staging row's codes are decoded with: INT8-asym -(1024 + zero point), MX the block's
+// scale (MXINT8 as two half-precision powers of two).
+struct ActDecode {
+    half2v negz;
+    float scale;
+    half2v f1, f2;
+};
+
+// E8M0 byte e8 relative to a row whose largest is emax, ebias = 141 - emax: the block scale
+// 2^(e8 - emax + 14) puts the largest block in [2^14, 2^15), so blocks down to 2^-28 of it stay
+// normal in half precision.  Scales below 2^-126 only decode to zeros and are clamped there.
 template <int AF>
-CHAM_DEV uint4 decode_act8(uint32_t w0, uint32_t w1, half2v negz) {
+CHAM_DEV ActDecode mx_decode(int e8, int ebias) {
+    ActDecode d;
+    const int b = max(e8 + ebias, 1);  // binary32 exponent field of the scale
+    d.scale = __uint_as_float((uint32_t)b << 23);
+    if (AF == CHAM_A_MXINT8) {  // 6 fraction bits; q 2^e1 is a normal half, times 2^e2 rounds once
+        const int e = b - 127 - 6, e1 = max(e, -14), e2 = max(e - e1, -24);
+        const _Float16 a = (_Float16)__uint_as_float((uint32_t)(e1 + 127) << 23);
+        const _Float16 c = (_Float16)__uint_as_float((uint32_t)(e2 + 127) << 23);
+        d.f1 = half2v{a, a};
+        d.f2 = half2v{c, c};
+    }
+    return d;
+}
+
+// 8 activation codes (k0..k3 in w0, k4..k7 in w1) -> 8 halves in that order; exact for the
+// per-tensor formats, rounded to half precision once (blocks far below the largest) for MX.
+template <int AF>
+CHAM_DEV uint4 decode_act8(uint32_t w0, uint32_t w1, const ActDecode& p) {
     // byte selectors of v_perm_b32(w1, w0, sel): 0..3 -> k0..k3, 4..7 -> k4..k7, 12 -> 0
     uint32_t d[4];
-    if (AF == kAE5M2) {  // E5M2 is the top byte of binary16
+    if (AF == CHAM_A_FP8_E5M2) {  // E5M2 is the top byte of binary16
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             d[j] = __builtin_amdgcn_perm(w1, w0, 0x0Cu | ((uint32_t)(2 * j) << 8) | (0x0Cu << 16) | ((uint32_t)(2 * j + 1) << 24));
-    } else if (AF == kAE4M3) {  // hardware E4M3 -> binary16 conversion, unit scale
-        d[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, false));
-        d[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, 1.0f, true));
-        d[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, false));
-        d[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, 1.0f, true));
-    } else {  // INT8-asym: (1024 + c) - (1024 + z) in binary16
+    } else if (AF == CHAM_A_FP8_E4M3 || AF == CHAM_A_MXFP8_E4M3) {  // hardware E4M3 -> binary16 conversion
+        const float sc = AF == CHAM_A_FP8_E4M3 ? 1.0f : p.scale;
+        d[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, sc, false));
+        d[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w0, sc, true));
+        d[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, sc, false));
+        d[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w1, sc, true));
+    } else {  // INT8-asym: (1024 + c) - (1024 + z); MXINT8: (1024 + (c ^ 128)) - 1152 = c, times the block scale
+        const half2v off = AF == CHAM_A_MXINT8 ? half2v{(_Float16)-1152.0f, (_Float16)-1152.0f} : p.negz;
+        if (AF == CHAM_A_MXINT8) {
+            w0 ^= 0x80808080u;
+            w1 ^= 0x80808080u;
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint32_t v = __builtin_amdgcn_perm(w1, w0, (uint32_t)(2 * j) | (0x0Cu << 8) | ((uint32_t)(2 * j + 1) << 16) | (0x0Cu << 24)) | 0x64006400u;
-            d[j] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, v) + negz);
+            half2v r = __builtin_bit_cast(half2v, v) + off;
+            if (AF == CHAM_A_MXINT8) r = (r * p.f1) * p.f2;
+            d[j] = __builtin_bit_cast(uint32_t, r);
         }
     }
     return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-// NW wavefronts side by side, each TM x TN blocks of 32 x 32 outputs.
-template <int TM, int TN, int NW, int AF>
+// INT8-asym codes of the convolution whose zero point is beyond +-1024: q - z in binary32, times
+// the power of two f that keeps it within half precision's range, rounded to half precision.
+CHAM_DEV uint4 decode_act8_far(uint32_t w0, uint32_t w1, float z, float f) {
+    uint32_t d[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t w = (j < 2 ? w0 : w1) >> (16 * (j & 1));
+        d[j] = half_pair2(((float)(w & 0xFFu) - z) * f, ((float)((w >> 8) & 0xFFu) - z) * f);
+    }
+    return make_uint4(d[0], d[1], d[2], d[3]);
+}
+
+// NW wavefronts side by side, each TM x TN blocks of 32 x 32 outputs; AF the activation format
+// (CHAM_A_*), CONV the 3x3 convolution.
+template <int TM, int TN, int NW, int AF, bool CONV>
 __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) void gemm_kernel(GemmArgs a) {
     constexpr int NT = 64 * NW;
     constexpr int BM = 32 * TM;
     constexpr int BN = tile_width(TN, NW);
-    constexpr bool HALF = AF == kAF16 || AF == kAConv;   // the operand comes in half precision
-    constexpr int AL = BM * (HALF ? 8 : 4);              // 16-byte activation loads per k-step
-    constexpr int AQ = (AL + NT - 1) / NT;               // of them, per thread
-    constexpr bool AFULL = AQ * NT == AL;                // every load falls inside the tile
-    constexpr int ARH = HALF ? 8 : 4;                    // loads per row
-    constexpr int RSTEP = NT / ARH;                      // rows between a thread's loads
+    constexpr bool MX = mx_act(AF);
+    constexpr bool INT8 = AF == CHAM_A_INT8_ASYM;
+    constexpr bool CORR = INT8 && !CONV;                 // zero-point correction in the epilogue
+    constexpr int AL = BM * 4;                           // 16-byte activation loads per k-step
+    constexpr int AQ = AL / NT;                          // of them, per thread
+    static_assert(AQ * NT == AL && NT % BM == 0, "every load falls inside the tile");
+    constexpr int RSTEP = NT / 4;                        // rows between a thread's loads
     __shared__ uint4 lds[2][BM * 8];
     __shared__ __align__(16) float Rs[BM];
-    __shared__ __align__(16) float Rc[AF == kAInt8 ? BM : 4];
+    __shared__ __align__(16) float Rc[CORR ? BM : 4];
+    __shared__ int Re[MX ? (CONV ? NW : BM) : 1];        // largest block exponents
 
     const int t = threadIdx.x;
     const int lane = t & 63, wave = t >> 6;
@@ -598,96 +542,121 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
     const int kb = split * a.kchunk;
     const int nsteps = K / BK - kb < a.kchunk ? K / BK - kb : a.kchunk;
 
-    // per-row activation scale (the row's sample's s; MX: the pre-pass's row scale).
+    // per-row activation scale (the row's sample's s; MX: set below).
     // INT8-asym: codes are decoded as (1024 + c) - (1024 + z1) with z1 the sample's zero point
     // clamped to [-1024, 1024] (exact in half precision); the rest z - z1 (an integer, exact
     // in binary32) is taken out in the epilogue as -(z - z1) s times the channel's weight sum
-    // (split 0 only).
+    // (split 0 only).  The convolution's rows miss taps at the borders, so a zero point beyond
+    // +-1024 is taken out while decoding there, rounded to half precision.
     for (int r = t; r < BM; r += NT) {
         const int m = r < rows ? m0 + r : m0;
-        if (HALF) {
-            Rs[r] = a.rowscale[m];
-        } else {
+        if (!MX) {
             Rs[r] = a.xs[m / a.rps];
-            if (AF == kAInt8) {
+            if (CORR) {
                 const float za = a.xz[m / a.rps], z1 = clampf(za, -1024.0f, 1024.0f);
                 Rc[r] = split == 0 ? -((za - z1) * a.xs[m / a.rps]) : 0.0f;
             }
+            if (INT8 && CONV) Rs[r] = ldexpf(Rs[r], far_eref(a.xz[m / a.rps]));
         }
     }
-    // the staging rows of this thread: their -(1024 + z1)
-    half2v negz[AF == kAInt8 ? AQ : 1];
+    // the staging rows of this thread: their -(1024 + z1), or what far zero points take
+    half2v negz[INT8 ? AQ : 1];
+    float farz[INT8 && CONV ? AQ : 1], farf[INT8 && CONV ? AQ : 1];
+    bool far = false;
 #pragma unroll
-    for (int i = 0; i < (AF == kAInt8 ? AQ : 1); ++i) {
+    for (int i = 0; i < (INT8 ? AQ : 1); ++i) {
         negz[i] = half2v{(_Float16)0.0f, (_Float16)0.0f};
-        if (AF == kAInt8) {
-            const int r = t / ARH + RSTEP * i;
+        if (INT8) {
+            const int r = t / 4 + RSTEP * i;
             const int m = r < rows ? m0 + r : m0;
-            const _Float16 nz = (_Float16)(-(1024.0f + clampf(a.xz[m / a.rps], -1024.0f, 1024.0f)));
+            const float za = a.xz[m / a.rps];
+            const _Float16 nz = (_Float16)(-(1024.0f + clampf(za, -1024.0f, 1024.0f)));
             negz[i] = half2v{nz, nz};
+            if (CONV) {
+                farz[i] = za;
+                farf[i] = ldexpf(1.0f, -far_eref(za));
+                far |= fabsf(za) > 1024.0f;
+            }
         }
     }
+    if (INT8 && CONV) far = __any(far);  // wavefront-uniform
 
     // ---- activation tile: global -> registers two k-steps ahead -> LDS, 16-byte loads
     // through a buffer resource whose range check returns zeros past the last row.  The
     // tile is stored as rows of 8 logical 16-byte chunks (8 k each), chunk c of row r at
-    // slot c ^ ((r >> 1) & 7).
-    //  half-precision copy: load q = NT i + t is row q >> 3, chunk q & 7;
-    //  codes: load q is row q >> 2, codes 16 (q & 3) .. + 15 = chunks 2 (q & 3), + 1.
+    // slot c ^ ((r >> 1) & 7); load q = NT i + t is row q >> 2, codes 16 (q & 3) .. + 15 =
+    // chunks 2 (q & 3), + 1.  MX: the exponent byte of the load's block comes with it.
+    const int CK = CONV ? a.C : K;  // codes per row in memory
     const __amdgpu_buffer_rsrc_t ra =
-        AF == kAConv ? __builtin_amdgcn_make_buffer_rsrc((void*)a.Xh, (short)0, (int)a.xh_bytes, kBufferFlags)
-        : AF == kAF16 ? __builtin_amdgcn_make_buffer_rsrc((void*)(a.Xh + (int64_t)m0 * K + kb * BK), (short)0,
-                                                          (rows * K - kb * BK) * 2, kBufferFlags)
-                      : __builtin_amdgcn_make_buffer_rsrc((void*)(a.xc + (int64_t)m0 * K + kb * BK), (short)0,
-                                                          rows * K - kb * BK, kBufferFlags);
-    const uint32_t acol = HALF ? (uint32_t)(((t & 7) ^ ((t >> 4) & 7)) << 4) : (uint32_t)((t & 3) << 4);
-    const uint32_t aoff0 = (uint32_t)((t / ARH) * K * (HALF ? 2 : 1)) + acol;
-    // convolution: the padded pixel of each staging row at tap (0, 0); rows past the tile's
-    // last take an offset past the buffer (loads return zeros)
-    int pix[AF == kAConv ? AQ : 1];
+        CONV ? __builtin_amdgcn_make_buffer_rsrc((void*)a.xc, (short)0, a.M * CK, kBufferFlags)
+             : __builtin_amdgcn_make_buffer_rsrc((void*)(a.xc + (int64_t)m0 * K + kb * BK), (short)0, rows * K - kb * BK, kBufferFlags);
+    const __amdgpu_buffer_rsrc_t re = __builtin_amdgcn_make_buffer_rsrc(
+        MX ? (void*)(a.xe8 + (CONV ? 0 : (int64_t)m0 * (K / 32) + kb * 2)) : (void*)a.xc, (short)0,
+        MX ? (CONV ? a.M * (CK / 32) : rows * (K / 32) - kb * 2) : 0, kBufferFlags);
+    const uint32_t aoff0 = (uint32_t)((t / 4) * K + ((t & 3) << 4));
+    // convolution: the offset of each staging row's pixel, and the taps that fall inside its image (none for
+    // rows past the tile's last)
+    int pix[CONV ? AQ : 1];
+    uint32_t taps[CONV ? AQ : 1];
 #pragma unroll
-    for (int i = 0; i < (AF == kAConv ? AQ : 1); ++i) {
-        pix[i] = -1;
-        if (AF == kAConv) {
-            const int r = t / ARH + RSTEP * i;
-            if (r < rows) {
-                const int m = m0 + r, x = m % a.W, yb = m / a.W, y = yb % a.H, b = yb / a.H;
-                pix[i] = (b * (a.H + 2) + y) * (a.W + 2) + x;
-            }
+    for (int i = 0; i < (CONV ? AQ : 1); ++i) {
+        pix[i] = 0;
+        taps[i] = 0;
+        const int r = t / 4 + RSTEP * i;
+        if (CONV && r < rows) {
+            const int m = m0 + r, x = m % a.W, y = m / a.W % a.H;
+            pix[i] = m * a.C + ((t & 3) << 4);
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                if ((unsigned)(y + q / 3 - 1) < (unsigned)a.H && (unsigned)(x + q % 3 - 1) < (unsigned)a.W) taps[i] |= 1u << q;
         }
     }
     struct AStage {
         uint4 v[AQ];
+        uint32_t e[AQ];  // MX: the block's exponent byte; INT8-asym convolution: the tap is inside
     };
     auto load_a = [&](AStage& S, int k) __attribute__((always_inline)) {
-        int tapoff = 0, ci0 = 0;
-        if (AF == kAConv) {  // k-step -> tap (ky, kx) and channel offset (C % 64 == 0)
-            const int kk = (kb + k) * BK, tap = kk / a.C;
-            ci0 = kk - tap * a.C;
-            tapoff = (tap / 3) * (a.W + 2) + tap % 3;
+        int tap = 0, tapoff = 0;
+        if (CONV) {  // k-step -> tap (ky, kx) and channel offset (C % 64 == 0)
+            const int kk = (kb + k) * BK;
+            tap = kk / a.C;
+            const int ci0 = kk - tap * a.C;
+            tapoff = ((tap / 3 - 1) * a.W + tap % 3 - 1) * a.C + ci0;
         }
 #pragma unroll
         for (int i = 0; i < AQ; ++i) {
             uint32_t off;
-            if (AF == kAConv) off = pix[i] < 0 ? 0x7FFFFFF0u : (uint32_t)(((pix[i] + tapoff) * a.C + ci0) * 2) + acol;
-            else off = aoff0 + (uint32_t)(i * RSTEP * K + k * BK) * (HALF ? 2u : 1u);
-            S.v[i] = (!AFULL && i * NT + t >= AL)
-                         ? make_uint4(0u, 0u, 0u, 0u)
-                         : __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)off, 0, 0));
+            if (CONV) {  // outside the image: past both buffers, also as a block index
+                const bool in = (taps[i] >> tap) & 1u;
+                off = in ? (uint32_t)(pix[i] + tapoff) : 0x7FFFFFF0u;
+                if (INT8) S.e[i] = in ? 1u : 0u;
+            } else {
+                off = aoff0 + (uint32_t)(i * RSTEP * K + k * BK);
+            }
+            S.v[i] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)off, 0, 0));
+            if (MX) S.e[i] = __builtin_amdgcn_raw_buffer_load_b8(re, (int)(off >> 5), 0, 0);
         }
     };
+    int ebias[MX ? AQ : 1];  // of the staging rows (mx_decode)
     auto store_a = [&](const AStage& S, int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < AQ; ++i) {
             const int q = i * NT + t;
-            if (!AFULL && q >= AL) continue;
-            if (HALF) {
-                lds[buf][q] = S.v[i];
+            const int r = q >> 2, c = 2 * (q & 3), sw = (r >> 1) & 7;
+            uint4 d0, d1;
+            if (INT8 && CONV && far) {
+                d0 = decode_act8_far(S.v[i].x, S.v[i].y, farz[i], farf[i]);
+                d1 = decode_act8_far(S.v[i].z, S.v[i].w, farz[i], farf[i]);
             } else {
-                const int r = q >> 2, c = 2 * (q & 3), sw = (r >> 1) & 7;
-                lds[buf][r * 8 + (c ^ sw)] = decode_act8<AF>(S.v[i].x, S.v[i].y, negz[AF == kAInt8 ? i : 0]);
-                lds[buf][r * 8 + ((c + 1) ^ sw)] = decode_act8<AF>(S.v[i].z, S.v[i].w, negz[AF == kAInt8 ? i : 0]);
+                ActDecode p;
+                if (MX) p = mx_decode<AF>((int)S.e[i], ebias[i]);
+                p.negz = negz[INT8 ? i : 0];
+                d0 = decode_act8<AF>(S.v[i].x, S.v[i].y, p);
+                d1 = decode_act8<AF>(S.v[i].z, S.v[i].w, p);
             }
+            if (INT8 && CONV && !S.e[i]) d0 = d1 = make_uint4(0u, 0u, 0u, 0u);  // the padding is 0, not the code 0
+            lds[buf][r * 8 + (c ^ sw)] = d0;
+            lds[buf][r * 8 + ((c + 1) ^ sw)] = d1;
         }
     };
 
@@ -720,7 +689,7 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
         const int n = n0 + nl + 32 * j;
         cs[j] = n < N ? a.cols[n].colscale : 0.0f;
         csum[j] = 0.0f;
-        if (AF == kAInt8 && n < N)
+        if (CORR && n < N)
             for (int q = 0; q < a.nkc; ++q) csum[j] += a.colsum[(int64_t)q * N + n];
     }
 
@@ -750,7 +719,7 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
     // sub-step 1, behind the barrier, and the tile of step k + 2 is stored into this step's
     // buffer in sub-step 2.  Step indices past the end are clamped (harmless reloads).
     constexpr int LA = TM * TN <= 2 ? 3 : 1;
-    constexpr int WD = TM * TN <= (HALF ? 2 : 4) ? 2 : 1;
+    constexpr int WD = TM * TN <= (CONV ? (INT8 ? 0 : 2) : AF == CHAM_A_MXINT8 ? 2 : 4) ? 2 : 1;  // as registers allow
     const int klast = nsteps - 1;
     AStage R[2];
     half8 fr[LA + 1][TM], W[WD][4][TN];
@@ -765,6 +734,36 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
     if (WD == 2) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) load_w(W[WD - 1][s], 1 < klast ? 1 : klast, s);
+    }
+    if (MX) {
+        // the largest block exponent of each row over this split's k (convolution: of the run
+        // of pixels that holds every neighbour of the tile's rows), behind the first loads
+        if (CONV) {
+            const int p0 = max(m0 - a.W - 1, 0), p1 = min(m0 + rows + a.W + 1, a.M);
+            const int e0 = p0 * (CK / 32), e1 = p1 * (CK / 32);
+            int mx = 0;
+            for (int o = e0 + 16 * t; o < e1; o += 16 * NT) mx = max(mx, max_bytes(a.xe8, o, min(o + 16, e1)));
+            for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+            if (lane == 0) Re[wave] = mx;
+        } else {
+            constexpr int TPR = NT / BM;  // threads per row, consecutive lanes
+            const int r = t / TPR;
+            const uint8_t* row = a.xe8 + (int64_t)(m0 + (r < rows ? r : 0)) * (K / 32) + kb * 2;
+            int mx = 0;
+            for (int o = 16 * (t % TPR); o < 2 * nsteps; o += 16 * TPR) mx = max(mx, max_bytes(row, o, min(o + 16, 2 * nsteps)));
+#pragma unroll
+            for (int o = 1; o < TPR; o <<= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
+            if (t % TPR == 0) Re[r] = mx;
+        }
+        lds_barrier();
+        int tmax = 0;
+        if (CONV) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) tmax = max(tmax, Re[w]);
+        }
+#pragma unroll
+        for (int i = 0; i < (MX ? AQ : 1); ++i) ebias[i] = 141 - (CONV ? tmax : Re[t / 4 + RSTEP * i]);
+        for (int r = t; r < BM; r += NT) Rs[r] = ldexpf(1.0f, (CONV ? tmax : Re[r]) - 141);
     }
     store_a(R[0], 0);
     if (LA == 3) {
@@ -827,7 +826,7 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
         for (int q = 0; q < 4; ++q) {
             const float4 v = *reinterpret_cast<const float4*>(&Rs[32 * i + 8 * q + 4 * h]);
             rs[4 * q] = v.x; rs[4 * q + 1] = v.y; rs[4 * q + 2] = v.z; rs[4 * q + 3] = v.w;
-            if (AF == kAInt8) {
+            if (CORR) {
                 const float4 c = *reinterpret_cast<const float4*>(&Rc[32 * i + 8 * q + 4 * h]);
                 rc[4 * q] = c.x; rc[4 * q + 1] = c.y; rc[4 * q + 2] = c.z; rc[4 * q + 3] = c.w;
             }
@@ -841,7 +840,7 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
                 for (int r = 0; r < 16; ++r) {
                     // (acc rs) cs, plus the zero-point correction of INT8-asym activations
                     float v = (acc[i][j][r] * rs[r]) * cs[j];
-                    if (AF == kAInt8) v = v + rc[r] * csum[j];
+                    if (CORR) v = v + rc[r] * csum[j];
                     const uint32_t bits = __builtin_bit_cast(uint32_t, v);
                     const int soff = (8 * (r >> 2) + (r & 3)) * N * 4;
                     if (cached) __builtin_amdgcn_raw_buffer_store_b32(bits, ro, voff, soff, 0);
@@ -971,12 +970,23 @@ size_t split_bytes(int64_t M, int64_t N, int64_t K) {
     return p.splits > 1 ? (size_t)p.splits * (size_t)M * (size_t)N * 4 : 0;
 }
 
-template <int AF>
+template <int AF, bool CONV>
 void launch_gemm_af(const GemmArgs& a, int tile, unsigned grid, hipStream_t s) {
     switch (tile) {
-    case 0: hipLaunchKernelGGL((gemm_kernel<4, 2, 4, AF>), dim3(grid), dim3(256), 0, s, a); break;
-    case 1: hipLaunchKernelGGL((gemm_kernel<4, 1, 4, AF>), dim3(grid), dim3(256), 0, s, a); break;
-    default: hipLaunchKernelGGL((gemm_kernel<2, 1, 4, AF>), dim3(grid), dim3(256), 0, s, a); break;
+    case 0: hipLaunchKernelGGL((gemm_kernel<4, 2, 4, AF, CONV>), dim3(grid), dim3(256), 0, s, a); break;
+    case 1: hipLaunchKernelGGL((gemm_kernel<4, 1, 4, AF, CONV>), dim3(grid), dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((gemm_kernel<2, 1, 4, AF, CONV>), dim3(grid), dim3(256), 0, s, a); break;
+    }
+}
+
+template <bool CONV>
+void launch_gemm_fmt(const GemmArgs& a, int af, int tile, unsigned grid, hipStream_t s) {
+    switch (af) {
+    case CHAM_A_INT8_ASYM: launch_gemm_af<CHAM_A_INT8_ASYM, CONV>(a, tile, grid, s); break;
+    case CHAM_A_FP8_E4M3: launch_gemm_af<CHAM_A_FP8_E4M3, CONV>(a, tile, grid, s); break;
+    case CHAM_A_FP8_E5M2: launch_gemm_af<CHAM_A_FP8_E5M2, CONV>(a, tile, grid, s); break;
+    case CHAM_A_MXFP8_E4M3: launch_gemm_af<CHAM_A_MXFP8_E4M3, CONV>(a, tile, grid, s); break;
+    default: launch_gemm_af<CHAM_A_MXINT8, CONV>(a, tile, grid, s); break;
     }
 }
 
@@ -998,13 +1008,8 @@ void launch_gemm(GemmArgs a, int tile, int af, hipStream_t s) {
     a.gm = group_rows(mt, a.tn);
     a.cached = a.splits > 1 || (a.N & 31) != 0;
     const unsigned grid = (unsigned)(mt * a.tn * a.splits);
-    switch (af) {
-    case kAInt8: launch_gemm_af<kAInt8>(a, tile, grid, s); break;
-    case kAE4M3: launch_gemm_af<kAE4M3>(a, tile, grid, s); break;
-    case kAE5M2: launch_gemm_af<kAE5M2>(a, tile, grid, s); break;
-    case kAConv: launch_gemm_af<kAConv>(a, tile, grid, s); break;
-    default: launch_gemm_af<kAF16>(a, tile, grid, s); break;
-    }
+    if (a.C > 0) launch_gemm_fmt<true>(a, af, tile, grid, s);
+    else launch_gemm_fmt<false>(a, af, tile, grid, s);
 }
 
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
@@ -1184,28 +1189,25 @@ struct ConvSpec {
     int B, H, W;
 };
 
-// Workspace of the convolution: the padded half-precision copy, the row scales, the block
-// exponent maximum, the weights' layout (no packed layout given) and the k-split partials.
+// Workspace of the convolution: what ws_layout reserves for activations, the weights' layout
+// (no packed layout given) and the k-split partials.
 static size_t conv_workspace(int64_t B, int64_t H, int64_t W, int64_t C, int64_t Co) {
     const int64_t M = B * H * W;
     return align256((size_t)(B * (H + 2) * (W + 2) * C) * 2) + align256((size_t)M * 4) + 256 +
            align256(cham_packed_bytes(Co, 9 * C)) + split_bytes(M, Co, 9 * C);
 }
 
-// What one call uses of its workspace, in this order: the half-precision activation copy
-// and row scales (MX activations and the convolution only), the block exponent maximum
-// (convolution), the weight layout (when no packed layout comes with the weight) and the
-// k-split partials (when the plan splits).
+// What one call uses of its workspace: the weight layout (when no packed layout comes with the
+// weight) and the k-split partials (when the plan splits).  MX activations and the convolution
+// reserve room for a half-precision activation copy and its scales in front: nothing is written
+// there, but the sizes that callers are told, and below which a call is refused, include it.
 struct WsLayout {
-    size_t xh, rs, emax, rec, part, total;
+    size_t rec, part, total;
 };
 static WsLayout ws_layout(bool half_copy, size_t xh_bytes, bool conv, bool packed, int64_t M, int64_t N, int64_t K,
                           int splits) {
     WsLayout l;
-    l.xh = 0;
-    l.rs = l.xh + (half_copy ? align256(xh_bytes) : 0);
-    l.emax = l.rs + (half_copy ? align256((size_t)M * 4) : 0);
-    l.rec = l.emax + (conv ? 256 : 0);
+    l.rec = (half_copy ? align256(xh_bytes) + align256((size_t)M * 4) : 0) + (conv ? 256 : 0);
     l.part = l.rec + (packed ? 0 : align256(cham_packed_bytes(N, K)));
     l.total = l.part + (splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * 4 : 0);
     return l;
@@ -1262,35 +1264,16 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
     hipStream_t s = (hipStream_t)stream;
 
     char* w = (char*)ws;
-    _Float16* Xh = (_Float16*)(w + wl.xh);
-    float* rowscale = (float*)(w + wl.rs);
-    int* emax = (int*)(w + wl.emax);
     // the search's packed layout replaces the pre-pass
     const Layout lay = layout_at(wq->packed ? wq->packed : (void*)(w + wl.rec), N, K);
     float* part = (float*)(w + wl.part);
-
-    if (cv) {
-        if (amx) {
-            hipLaunchKernelGGL(emax_kernel, dim3(1), dim3(1024), 0, s, xq->e8m0, xq->M * (xq->K / 32), emax);
-            CHAM_CHECK_LAUNCH();
-        }
-        PrepConvArgs p{xq->codes, xq->e8m0, xq->fmt, cv->B, cv->H, cv->W, (int)xq->K, xq->scale,
-                       xq->zero, (int)(xq->M / xq->nsamples), emax, Xh, rowscale};
-        hipLaunchKernelGGL(prep_conv_kernel, dim3((unsigned)(cv->B * (cv->H + 2) * (cv->W + 2))), dim3(256), 0, s, p);
-        CHAM_CHECK_LAUNCH();
-    } else if (amx) {
-        PrepArgs p{xq->codes, xq->e8m0, xq->fmt, M, K, Xh, rowscale};
-        hipLaunchKernelGGL(prep_kernel, dim3((unsigned)M), dim3(256), 0, s, p);
-        CHAM_CHECK_LAUNCH();
-    }
 
     if (!wq->packed) launch_records(v, lay, s);
     CHAM_CHECK_LAUNCH();
 
     GemmArgs a;
-    a.Xh = Xh;
-    a.rowscale = rowscale;
     a.xc = xq->codes;
+    a.xe8 = xq->e8m0;
     a.xs = xq->scale;
     a.xz = xq->zero;
     a.rps = M / xq->nsamples;
@@ -1309,13 +1292,9 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
     a.H = cv ? cv->H : 0;
     a.W = cv ? cv->W : 0;
     a.C = cv ? (int)xq->K : 0;
-    a.xh_bytes = (uint32_t)xh_bytes;
-    const int af = cv ? kAConv
-                 : amx ? kAF16
-                       : (xq->fmt == CHAM_A_INT8_ASYM ? kAInt8 : (xq->fmt == CHAM_A_FP8_E4M3 ? kAE4M3 : kAE5M2));
     a.splits = plan.splits;
     a.kchunk = kchunk;
-    launch_gemm(a, plan.tile, af, s);
+    launch_gemm(a, plan.tile, xq->fmt, s);
     CHAM_CHECK_LAUNCH();
     if (plan.splits > 1) {
         const int64_t MN = (int64_t)M * N;

@@ -85,3 +85,28 @@ def test_conv3x3_shortcut_conv1_mxfp8_sampled():
     Yr, Bm = oracle.linear_pairs(cols, Wh, np.arange(S), nn)
     rel = np.abs(Y[pix, nn].astype(np.float64) - Yr) / np.maximum(Bm, 1e-300)
     assert rel.max() <= 1e-3, rel.max()
+
+
+@pytest.mark.parametrize("fmt", [cham.A_MXFP8, cham.A_MXINT8, cham.A_INT8_ASYM])
+@pytest.mark.parametrize("B,H,W,C,Co", [(1, 1, 1, 64, 5), (3, 1, 40, 128, 33), (2, 13, 3, 64, 130), (1, 20, 20, 192, 320)])
+def test_conv3x3_codes_decoded_while_staged(fmt, B, H, W, C, Co):
+    """Images of one pixel, one line and narrow ones (tiles that straddle lines and images), a
+    k-split; block scales 2^24 apart within and between images; and zero points within and
+    beyond +-1024 in one batch (INT8-asym), with the padding at zero for all."""
+    g = np.random.default_rng(B + H + W + C)
+    X = g.standard_t(4, (B, H, W, C)).astype(np.float32)
+    if fmt == cham.A_INT8_ASYM:
+        X[-1] = np.float32(300.0) + np.abs(X[-1]) / np.abs(X[-1]).max()  # last image: z about -76500
+    else:
+        X *= np.exp2(g.integers(-12, 13, (B, H, W, C // 32))).repeat(32, axis=3).astype(np.float32)
+    Wt, _ = synth.hetero_weights(2, Co, 9 * C)
+    wp = cham.select_weight_formats(torch.from_numpy(Wt).to(DEV), cham.MASK_W4, want_packed=True)
+    ref = oracle.select_weight_formats(Wt, cham.MASK_W4, want_err=False, want_perm=False)
+    case(f"conv3x3 staged decode B={B} H={H} W={W} C={C} Co={Co} fmt={fmt}")
+    xq = cham.quantize_act(torch.from_numpy(X.reshape(-1, C)).to(DEV), fmt, dynamic=True, nsamples=B)
+    Y = _np(cham.conv3x3_mixed(xq, B, H, W, wp)).astype(np.float64)
+    _, _, xh, _, _ = oracle.quantize_act_per_sample(X.reshape(-1, C), fmt, B, want_xhat=True)
+    Yr, Bm = oracle.conv3x3(xh.reshape(B, H, W, C), oracle.dequant_weights(ref, 9 * C))
+    # 2^-11 per half-precision weight and, beyond +-1024, activation
+    rel = np.abs(Y - Yr.reshape(-1, Co)) / np.maximum(Bm.reshape(-1, Co), 1e-300)
+    assert rel.max() <= 1e-3, rel.max()

@@ -288,3 +288,40 @@ def test_linear_exact_workspace(afmt, packed, M, N, K):
         with pytest.raises(cham.ChamError) as ei:
             cham.mixed_linear(xq, wq, ws=short)
         assert ei.value.status == cham.EWORKSPACE
+
+
+@pytest.mark.parametrize("fmt", [cham.A_MXFP8, cham.A_MXINT8])
+def test_mx_codes_to_half_precision_exact(fmt):
+    """Every finite element code at every block exponent from the row's largest down to 2^-48 of
+    it, through one-hot weights: the product is the element scaled to the row's reference
+    (largest block at 2^14) and rounded once to half precision, subnormals included, exactly."""
+    c = np.arange(256, dtype=np.uint8)
+    if fmt == cham.A_MXFP8:
+        v = np.array([oracle.mf_decode(oracle.MF_E4M3, int(x)) for x in c])
+        v[[0x7F, 0xFF]] = np.nan
+        keep = np.isfinite(v) & (np.abs(v) < 4.0)  # the quantizer's elements are below 2; 4 2^14 fits half
+        c, v = c[keep], v[keep].astype(np.float64)
+    else:
+        v = c.astype(np.int8).astype(np.float64) / 64.0
+    n = (c.size + 31) // 32 * 32
+    c, v = np.resize(c, n), np.resize(v, n)
+    K, top, D = 64 * ((n + 32 + 63) // 64), 200, 49
+    M, N = 3 * D, n
+    codes = np.zeros((M, K), np.uint8)
+    e8 = np.zeros((M, K // 32), np.uint8)
+    d = np.arange(M) % D
+    codes[:, 32:32 + n] = c
+    e8[:, 0] = top
+    e8[:, 1:1 + n // 32] = (top - d)[:, None]
+    W = np.zeros((N, K), np.float32)
+    W[np.arange(N), 32 + np.arange(N)] = 1.0
+    case(f"mx half precision fmt={fmt} M={M} N={N} K={K}")
+    wq = cham.select_weight_formats(torch.from_numpy(W).to(DEV), 1 << cham.W_MXFP4, want_packed=True)
+    aq = cham.alloc_aq(M, K, DEV)
+    aq.fmt = fmt
+    aq.codes.copy_(torch.from_numpy(codes))
+    aq.e8m0.copy_(torch.from_numpy(e8))
+    Y = _np(cham.mixed_linear(aq, wq))
+    with np.errstate(over="ignore"):
+        h = (v[None, :] * np.exp2(14.0 - d)[:, None]).astype(np.float16).astype(np.float64)
+    assert np.array_equal(Y.astype(np.float64), h * 2.0 ** (top - 127 - 14))
