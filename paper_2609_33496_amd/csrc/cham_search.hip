@@ -899,6 +899,32 @@ __global__ __launch_bounds__(256) void search_oct_kernel(SearchBatch B) {
     if (n < a.N) search_oct<MASK, NCH, LPC>(a, cells, n, (int)threadIdx.x % LPC);  // uniform per lane group
 }
 
+// Rows of up to 1280 and of up to 5120 elements in one launch: the long rows' workgroups, one
+// wavefront per channel, come first, and the short rows' fill the CUs that they leave idle.
+template <uint32_t MASK>
+__global__ __launch_bounds__(256) void search_oct_mixed_kernel(SearchBatch B) {
+    __shared__ NF4Cell cells[33];
+    nf4_cells_init(cells);
+    __syncthreads();
+    const int64_t b = blockIdx.x;
+    int i = 0;
+    while (i + 1 < B.nl && b >= B.wg_end[i]) ++i;
+    const SearchArgs& a = B.l[i];
+    const int64_t lb = b - (i ? B.wg_end[i - 1] : 0);
+    const int lpc = a.lpc == 64 ? 64 : 32;  // workgroup-uniform
+    const int64_t n = lb * (256 / lpc) + (int)threadIdx.x / lpc;
+    if (n >= a.N) return;
+    if (lpc == 64) search_oct<MASK, 10, 64>(a, cells, n, (int)threadIdx.x % 64);
+    else search_oct<MASK, 5, 32>(a, cells, n, (int)threadIdx.x % 32);
+}
+
+void launch_oct_mixed(const SearchBatch& B, uint32_t mask, hipStream_t s) {
+    const dim3 grid((unsigned)B.wg_end[B.nl - 1]);
+    if (mask == CHAM_MASK_W4) hipLaunchKernelGGL((search_oct_mixed_kernel<CHAM_MASK_W4>), grid, dim3(256), 0, s, B);
+    else if (mask == CHAM_MASK_W8) hipLaunchKernelGGL((search_oct_mixed_kernel<CHAM_MASK_W8>), grid, dim3(256), 0, s, B);
+    else hipLaunchKernelGGL((search_oct_mixed_kernel<0u>), grid, dim3(256), 0, s, B);
+}
+
 template <int NCH, int LPC>
 void launch_oct(const SearchBatch& B, uint32_t mask, hipStream_t s) {
     const dim3 grid((unsigned)B.wg_end[B.nl - 1]);
@@ -950,6 +976,15 @@ Variant variant_of(int64_t N, int64_t K) {
         if (nch <= c) { r = c; break; }
     return Variant{split, r, 0};
 }
+
+// Variants that may share a launch (search_oct_mixed_kernel), and whether the layers do: the
+// launch pays where the long rows alone would leave the CUs idle (at most two workgroups per CU)
+// and the short rows, which lose wavefronts per SIMD to the long rows' registers, are at most
+// four times as many weights.  One block of width 1280 (long 320 workgroups, short rows three
+// times the weights) 81.5 -> 76.0 us, with 8-bit formats 79.7 -> 64.7; four such blocks in a
+// batch (1280 workgroups) 232.7 -> 270, so they keep two launches.
+constexpr int64_t kMixLongWgs = 512, kMixShortShare = 4;
+bool mixable(const Variant& v) { return v.lpc == 64 || (v.lpc == 32 && v.nch == 5); }
 
 void launch_variant(const Variant& v, const SearchBatch& B, uint32_t mask, hipStream_t s) {
     if (v.lpc == 16) {
@@ -1047,26 +1082,42 @@ extern "C" int cham_select_weight_formats_batch(const float* const* W, cham_wq* 
         const Variant v = variant_of(args[i].N, args[i].K);
         args[i].split = v.split;
         const uint32_t key = args[i].mask == CHAM_MASK_W4 || args[i].mask == CHAM_MASK_W8 ? args[i].mask : 0u;
-        SearchBatch B;
-        B.nl = 0;
-        int64_t wgs = 0;
+        // may this launch hold long and short rows?  (the layers that it would take)
+        int64_t long_wgs = 0, long_w = 0, short_w = 0;
         for (int j = i; j < nlayers; ++j) {
+            const Variant vj = variant_of(args[j].N, args[j].K);
+            const uint32_t kj = args[j].mask == CHAM_MASK_W4 || args[j].mask == CHAM_MASK_W8 ? args[j].mask : 0u;
+            if (done[j] || kj != key || !mixable(vj)) continue;
+            if (vj.lpc == 64) { long_wgs += (args[j].N + 3) / 4; long_w += args[j].N * args[j].K; }
+            else short_w += args[j].N * args[j].K;
+        }
+        const bool mix = mixable(v) && long_wgs <= kMixLongWgs && short_w <= kMixShortShare * long_w;
+        int pick[kBatchMax], np = 0, nlong = 0;
+        for (int j = i; j < nlayers && np < kBatchMax; ++j) {
             if (done[j]) continue;
             const Variant vj = variant_of(args[j].N, args[j].K);
             const uint32_t kj = args[j].mask == CHAM_MASK_W4 || args[j].mask == CHAM_MASK_W8 ? args[j].mask : 0u;
-            if (vj.nch != v.nch || vj.lpc != v.lpc || kj != key) continue;
+            if (kj != key || !((vj.nch == v.nch && vj.lpc == v.lpc) || (mix && mixable(vj)))) continue;
             args[j].split = vj.split;
             args[j].lpc = vj.lpc;
-            const int64_t per_wg = vj.lpc ? 256 / vj.lpc : (vj.split == 1 ? 4 : 1);  // channels per workgroup
-            wgs += (args[j].N + per_wg - 1) / per_wg;
-            B.l[B.nl] = args[j];
-            B.wg_end[B.nl] = wgs;
-            ++B.nl;
+            nlong += vj.lpc == 64;
+            pick[np++] = j;
             done[j] = true;
-            if (B.nl == kBatchMax) break;
+        }
+        std::stable_sort(pick, pick + np, [&](int x, int y) { return args[x].lpc > args[y].lpc; });
+        SearchBatch B;
+        B.nl = np;
+        int64_t wgs = 0;
+        for (int q = 0; q < np; ++q) {
+            const SearchArgs& l = args[pick[q]];
+            const int64_t per_wg = l.lpc ? 256 / l.lpc : (l.split == 1 ? 4 : 1);  // channels per workgroup
+            wgs += (l.N + per_wg - 1) / per_wg;
+            B.l[q] = l;
+            B.wg_end[q] = wgs;
         }
         // a mixed palette (key 0) reads each layer's mask at run time
-        launch_variant(v, B, key ? key : 0u, s);
+        if (nlong > 0 && nlong < np) launch_oct_mixed(B, key, s);
+        else launch_variant(v, B, key, s);
         CHAM_CHECK_LAUNCH();
     }
     for (int i = 0; i < nlayers; ++i) wq[i].code_bits = args[i].code_bits;

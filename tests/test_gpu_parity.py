@@ -873,3 +873,19 @@ def test_linear_random_shapes(seed):
     yr, bm = oracle.linear_pairs(xh, Wh, mm, nn)
     err = np.abs(Y[mm, nn] - yr)
     assert np.all(err <= 1e-3 * bm), (err / np.maximum(bm, 1e-300)).max()
+
+
+@pytest.mark.parametrize("mask", [oracle.MASK_W4, oracle.MASK_W8, 0x1FF])
+def test_search_batch_long_and_short_rows_share_a_launch(mask):
+    """Rows of at most 1280 elements beside rows of up to 5120 in one batch, in either order, with
+    whole and partial last workgroups: the outputs are those of one call per layer."""
+    shapes = [(1030, 832), (1026, 2624), (1033, 1280), (1024, 5120)]
+    Ws = [torch.from_numpy(synth.hetero_weights(60 + i, N, K)[0]).to(DEV) for i, (N, K) in enumerate(shapes)]
+    for order in ((0, 1, 2), (3, 0), (2, 1, 3), (1, 3)):  # the third: too many long rows to share
+        case(f"select_weight_formats_batch mask={mask:#x} layers={order}")
+        outs = cham.select_weight_formats_batch([Ws[i] for i in order], mask)
+        for i, o in zip(order, outs):
+            r = cham.select_weight_formats(Ws[i], mask)
+            for name in ("fmt", "codes", "scale", "zero", "nf4_absmax", "e8m0", "perm", "group_off"):
+                a, b = getattr(o, name), getattr(r, name)
+                assert (a is None) == (b is None) and (a is None or torch.equal(a, b)), (i, name)
