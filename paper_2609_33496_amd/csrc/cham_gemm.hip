@@ -481,8 +481,9 @@ CHAM_DEV uint4 decode_act8(uint32_t w0, uint32_t w1, const ActDecode& p) {
     return make_uint4(d[0], d[1], d[2], d[3]);
 }
 
-// INT8-asym codes of the convolution whose zero point is beyond +-1024: q - z in binary32, times
-// the power of two f that keeps it within half precision's range, rounded to half precision.
+// INT8-asym codes of the convolution whose zero point is beyond +-1024 or no integer (1024 + z
+// would lose its fraction in half precision): q - z in binary32, times the power of two f that
+// keeps it within half precision's range, rounded to half precision.
 CHAM_DEV uint4 decode_act8_far(uint32_t w0, uint32_t w1, float z, float f) {
     uint32_t d[4];
 #pragma unroll
@@ -575,7 +576,7 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
             if (CONV) {
                 farz[i] = za;
                 farf[i] = ldexpf(1.0f, -far_eref(za));
-                far |= fabsf(za) > 1024.0f;
+                far |= fabsf(za) > 1024.0f || za != rne(za);
             }
         }
     }

@@ -110,3 +110,23 @@ def test_conv3x3_codes_decoded_while_staged(fmt, B, H, W, C, Co):
     # 2^-11 per half-precision weight and, beyond +-1024, activation
     rel = np.abs(Y - Yr.reshape(-1, Co)) / np.maximum(Bm.reshape(-1, Co), 1e-300)
     assert rel.max() <= 1e-3, rel.max()
+
+
+def test_conv3x3_int8_zero_point_with_a_fraction():
+    """INT8-asym codes of another quantizer, whose zero point is no integer: q - z in binary32,
+    rounded to half precision (2^-11 of it, beside 2^-11 of the weight: 1e-3 of the sum)."""
+    B, H, W, C, Co = 2, 6, 5, 64, 40
+    g = np.random.default_rng(11)
+    codes = g.integers(0, 256, (B * H * W, C)).astype(np.uint8)
+    s, z = np.array([0.02, 0.03], np.float32), np.array([127.375, 0.625], np.float32)
+    Wt = np.abs(synth.hetero_weights(2, Co, 9 * C)[0])  # an error of z does not cancel over a channel
+    wq = cham.select_weight_formats(torch.from_numpy(Wt).to(DEV), cham.MASK_W4, want_packed=True)
+    Wh = oracle.dequant_weights(oracle.select_weight_formats(Wt, cham.MASK_W4, want_err=False, want_perm=False), 9 * C)
+    aq = cham.AQ(B * H * W, C, cham.A_INT8_ASYM, torch.from_numpy(codes).to(DEV), None, torch.from_numpy(s).to(DEV),
+                 torch.from_numpy(z).to(DEV), B)
+    case(f"conv3x3 fractional zero points B={B} H={H} W={W} C={C} Co={Co}")
+    Y = _np(cham.conv3x3_mixed(aq, B, H, W, wq)).astype(np.float64)
+    xh = ((codes.reshape(B, -1).astype(np.float32) - z[:, None]) * s[:, None]).reshape(B, H, W, C)
+    Yr, Bm = oracle.conv3x3(xh, Wh)
+    rel = np.abs(Y - Yr.reshape(-1, Co)) / np.maximum(Bm.reshape(-1, Co), 1e-300)
+    assert rel.max() <= 1e-3, rel.max()
