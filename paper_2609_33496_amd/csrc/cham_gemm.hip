@@ -737,13 +737,22 @@ __global__ __launch_bounds__(64 * NW, TM * TN >= 8 ? 2 : TM * TN >= 4 ? 3 : 4) v
         for (int s = 0; s < 4; ++s) load_w(W[WD - 1][s], 1 < klast ? 1 : klast, s);
     }
     if (MX) {
-        // the largest block exponent of each row over this split's k (convolution: of the run
-        // of pixels that holds every neighbour of the tile's rows), behind the first loads
+        // the largest block exponent of each row over this split's k (convolution: of the pixels
+        // that hold every neighbour of the tile's rows), behind the first loads
         if (CONV) {
-            const int p0 = max(m0 - a.W - 1, 0), p1 = min(m0 + rows + a.W + 1, a.M);
-            const int e0 = p0 * (CK / 32), e1 = p1 * (CK / 32);
+            // one run of pixels; for long lines one run per tap line, so that the scan stays in
+            // proportion to the tile (64 channels, 1 x 200000 pixels: 87.2 us with one run, 33.3
+            // with three; 1 x 1000000: 1179 and 144).  Lines whose pixels take at most three
+            // passes of the workgroup stay one run: three cost their latencies one after another
+            // (512 x 512: 45.0 with one, 46.9 with three; 64 x 4096: 45.0 with either).
+            const bool lines = a.W > rows + 2 && (a.W + 1) * (CK / 32) > 3 * 8 * NT;
             int mx = 0;
-            for (int o = e0 + 16 * t; o < e1; o += 16 * NT) mx = max(mx, max_bytes(a.xe8, o, min(o + 16, e1)));
+            for (int d = lines ? -1 : 0; d <= (lines ? 1 : 0); ++d) {
+                const int c0 = m0 + d * a.W, ext = lines ? 1 : a.W + 1;
+                const int p0 = max(c0 - ext, 0), p1 = min(c0 + rows + ext, a.M);
+                const int e0 = p0 * (CK / 32), e1 = p1 * (CK / 32);
+                for (int o = e0 + 16 * t; o < e1; o += 16 * NT) mx = max(mx, max_bytes(a.xe8, o, min(o + 16, e1)));
+            }
             for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, kWave));
             if (lane == 0) Re[wave] = mx;
         } else {

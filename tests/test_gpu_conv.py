@@ -88,10 +88,11 @@ def test_conv3x3_shortcut_conv1_mxfp8_sampled():
 
 
 @pytest.mark.parametrize("fmt", [cham.A_MXFP8, cham.A_MXINT8, cham.A_INT8_ASYM])
-@pytest.mark.parametrize("B,H,W,C,Co", [(1, 1, 1, 64, 5), (3, 1, 40, 128, 33), (2, 13, 3, 64, 130), (1, 20, 20, 192, 320)])
+@pytest.mark.parametrize("B,H,W,C,Co", [(1, 1, 1, 64, 5), (3, 1, 40, 128, 33), (2, 13, 3, 64, 130), (1, 20, 20, 192, 320),
+                                         (2, 3, 300, 64, 40), (1, 1, 3100, 64, 5), (1, 2, 3072, 64, 3)])
 def test_conv3x3_codes_decoded_while_staged(fmt, B, H, W, C, Co):
-    """Images of one pixel, one line and narrow ones (tiles that straddle lines and images), a
-    k-split; block scales 2^24 apart within and between images; and zero points within and
+    """Images of one pixel, one line and narrow ones (tiles that straddle lines and images), lines
+    longer than a tile, a k-split; block scales 2^24 apart within and between images; and zero points within and
     beyond +-1024 in one batch (INT8-asym), with the padding at zero for all."""
     g = np.random.default_rng(B + H + W + C)
     X = g.standard_t(4, (B, H, W, C)).astype(np.float32)
