@@ -1008,14 +1008,19 @@ void launch_gemm_fmt(const GemmArgs& a, int af, int tile, unsigned grid, hipStre
 // is a multiple of 8 each XCD keeps the same eighth of the weights in its L2 and whole rows are
 // written at one time (2048 x 10240 x 1280, cold: 57.6 us against 70.0 in groups of two;
 // 1024 x 10240 x 1280: 32.7 against 42.2), elsewhere every XCD walks all weights and it loses
-// (8192 x 3456 x 1152: 85.5 against 72.4).
-int group_rows(int mt, int tn) { return tn % 8 == 0 && tn >= 32 ? 0 : std::min(2, mt); }
+// (8192 x 3456 x 1152: 85.5 against 72.4).  From 3072 channels on, 384 per XCD, row-major wins at
+// every height (1000 x 3072 x 768: 9.1 us against 12.2 in groups of two; 2048 x 3072 x 1280: 21.2
+// against 24.1; 8192 x 6144 x 1280: 116 against 127; 4096 x 4096 x 640: 27.0 against 29.8); an
+// XCD's share of fewer channels does not always pay for the wider spread of its activation rows
+// (1000 x 2048 x 1280: 8.8 against 10.6, but 4096 x 2048 x 640, INT8: 17.4 against 16.5;
+// 8192 x 1024 x 1280: 29.2 against 26.4).
+int group_rows(int mt, int tn, int bn) { return tn % 8 == 0 && tn * bn >= 3072 ? 0 : std::min(2, mt); }
 
 void launch_gemm(GemmArgs a, int tile, int af, hipStream_t s) {
     const TileCost& c = kTileCosts[tile];
     const int mt = row_tiles(a.M, c);
     a.tn = col_tiles(a.N, c);
-    a.gm = group_rows(mt, a.tn);
+    a.gm = group_rows(mt, a.tn, c.bn());
     a.cached = a.splits > 1 || (a.N & 31) != 0;
     const unsigned grid = (unsigned)(mt * a.tn * a.splits);
     if (a.C > 0) launch_gemm_fmt<true>(a, af, tile, grid, s);
