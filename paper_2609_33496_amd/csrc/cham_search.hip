@@ -978,13 +978,27 @@ Variant variant_of(int64_t N, int64_t K) {
 }
 
 // Variants that may share a launch (search_oct_mixed_kernel), and whether the layers do: the
-// launch pays where the long rows alone would leave the CUs idle (at most two workgroups per CU)
-// and the short rows, which lose wavefronts per SIMD to the long rows' registers, are at most
-// four times as many weights.  One block of width 1280 (long 320 workgroups, short rows three
-// times the weights) 81.5 -> 76.0 us, with 8-bit formats 79.7 -> 64.7; four such blocks in a
-// batch (1280 workgroups) 232.7 -> 270, so they keep two launches.
-constexpr int64_t kMixLongWgs = 512, kMixShortShare = 4;
+// launch pays where the long rows alone would leave the CUs idle, and costs the short rows
+// wavefronts per SIMD, as they run in the long rows' registers.  So: at most 512 workgroups of long
+// rows (two per CU), short rows of at most four times their weights, and
+// - 4-bit palette, which loses most wavefronts: of at most 960 / (long workgroups) times;
+// - palette read at run time, whose 224 registers fit fewer workgroups: of at most a quarter where
+//   the long rows take more than 384.
+// From separate against shared launches of 139 batches per palette (long rows of 2688 - 5120
+// elements in 208 - 960 workgroups, short ones of 0.25 - 6 times the weights); inside the lines
+// none is slower, at them: 4-bit, 256 workgroups 3 times 55.4 -> 51.5 us, 320 3 times (a block of
+// width 1280) 67.2 -> 64.2, 448 2 times even, 512 3 times (two blocks of width 1024) 66.9 -> 76.0;
+// 8-bit, 512 3 times 59.5 -> 54.4, 4 times 3 % faster; run-time palette, 384 4 times 4 % faster,
+// 448 3 times up to 8 % slower.
+constexpr int64_t kMixLongWgs = 512, kMixLongWgsAny = 384, kMixShortShare = 4, kMixShareWgsW4 = 960;
 bool mixable(const Variant& v) { return v.lpc == 64 || (v.lpc == 32 && v.nch == 5); }
+
+// long and short rows' weights, the long ones' workgroups; key: their palette, 0 read at run time
+bool mix_pays(int64_t long_wgs, int64_t long_w, int64_t short_w, uint32_t key) {
+    if (long_wgs > kMixLongWgs || short_w > kMixShortShare * long_w) return false;
+    if (key == CHAM_MASK_W4) return (double)long_wgs * (double)short_w <= (double)kMixShareWgsW4 * (double)long_w;
+    return key != 0u || long_wgs <= kMixLongWgsAny || 4 * short_w <= long_w;
+}
 
 void launch_variant(const Variant& v, const SearchBatch& B, uint32_t mask, hipStream_t s) {
     if (v.lpc == 16) {
@@ -1082,7 +1096,10 @@ extern "C" int cham_select_weight_formats_batch(const float* const* W, cham_wq* 
         const Variant v = variant_of(args[i].N, args[i].K);
         args[i].split = v.split;
         const uint32_t key = args[i].mask == CHAM_MASK_W4 || args[i].mask == CHAM_MASK_W8 ? args[i].mask : 0u;
-        // may this launch hold long and short rows?  (the layers that it would take)
+        // may this launch hold long and short rows?  Counted over all layers left, not only those
+        // that this launch would take: a long layer that would run with others of its kind later
+        // stays with them (15 short layers, then 4 long: 72.1 us, the first long one with the
+        // short ones 76.4; run-time palette 150 and 180)
         int64_t long_wgs = 0, long_w = 0, short_w = 0;
         for (int j = i; j < nlayers; ++j) {
             const Variant vj = variant_of(args[j].N, args[j].K);
@@ -1091,7 +1108,7 @@ extern "C" int cham_select_weight_formats_batch(const float* const* W, cham_wq* 
             if (vj.lpc == 64) { long_wgs += (args[j].N + 3) / 4; long_w += args[j].N * args[j].K; }
             else short_w += args[j].N * args[j].K;
         }
-        const bool mix = mixable(v) && long_wgs <= kMixLongWgs && short_w <= kMixShortShare * long_w;
+        const bool mix = mixable(v) && mix_pays(long_wgs, long_w, short_w, key);
         int pick[kBatchMax], np = 0, nlong = 0;
         for (int j = i; j < nlayers && np < kBatchMax; ++j) {
             if (done[j]) continue;
