@@ -196,7 +196,7 @@ struct LutArgs {
 constexpr int kLutThreads = 1024;
 
 // One workgroup.  First the SNR at every bucket midpoint: alpha_bar_t = prod_{s<=t}
-// (1 - beta_s) as a product over a wavefront's lanes, one wavefront per bucket (binary64; its
+// (1 - beta_s) as a product over a wavefront's lanes, one or four wavefronts per bucket (binary64; its
 // rounding differs from a sequential product only in the last bits, so only an SNR within
 // ~1e-15 of a gate could route differently).  Then one thread per (layer, bucket): kurtosis,
 // route, ScaleZP; the moments are read first, behind the products.  Bound by latency, so what
@@ -204,6 +204,13 @@ constexpr int kLutThreads = 1024;
 // another, each a product tree over 256 threads between two barriers, took 9.6.
 constexpr int kLutMaxBuckets = 1024;
 
+// Wavefronts per bucket.  Up to 4 buckets of a long schedule take 4 each (one bucket of 1000, 4000
+// and 100000 steps 2.95, 4.0 and 37.5 us -> 2.64, 3.1 and 11.6); with few steps the longer tail
+// costs more than the shorter products save (4 buckets of 1000 steps 3.1 -> 3.3, of 2000
+// 4.0 -> 3.6; 3 of 1000 even).
+int lut_wavefronts(int B, int T) { return B <= 4 && T >= 500 * std::max(B, 2) ? 4 : 1; }
+
+template <int PER>
 __global__ __launch_bounds__(kLutThreads) void lut_kernel(LutArgs a) {
     __shared__ double snr_ws[kLutMaxBuckets];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -217,11 +224,12 @@ __global__ __launch_bounds__(kLutThreads) void lut_kernel(LutArgs a) {
     };
     if ((int)threadIdx.x < a.L * a.B) load(threadIdx.x);
     const double rT = a.T > 1 ? 1.0 / (double)(a.T - 1) : 0.0;
-    for (int b = wave; b < a.B; b += kLutThreads / 64) {
+    for (int u = wave; u < a.B * PER; u += kLutThreads / 64) {
+        const int b = u / PER;
         const int tb = (int)(((int64_t)(2 * b + 1) * a.T) / (2LL * a.B));
         double prod = 1.0;
 #pragma unroll 4
-        for (int s = lane; s <= tb; s += 64) {
+        for (int s = lane + 64 * (u % PER); s <= tb; s += 64 * PER) {
             // s / (T - 1): the product with the reciprocal, corrected by its remainder
             double frac = (double)s * rT;
             frac = fma(fma(-frac, (double)(a.T - 1), (double)s), rT, frac);
@@ -235,7 +243,7 @@ __global__ __launch_bounds__(kLutThreads) void lut_kernel(LutArgs a) {
             prod *= (1.0 - beta);
         }
         for (int o = 32; o > 0; o >>= 1) prod *= __shfl_xor(prod, o, kWave);
-        if (lane == 0) snr_ws[b] = prod / (1.0 - prod);
+        if (lane == 0) snr_ws[u] = PER == 1 ? prod / (1.0 - prod) : prod;
     }
     __syncthreads();
     for (int i = threadIdx.x; i < a.L * a.B; i += kLutThreads) {
@@ -248,7 +256,13 @@ __global__ __launch_bounds__(kLutThreads) void lut_kernel(LutArgs a) {
         const double m2 = e2 - mu * mu;
         const double m4 = e4 - 4.0 * mu * e3 + 6.0 * mu * mu * e2 - 3.0 * mu * mu * mu * mu;
         const double kap = m4 / (m2 * m2);
-        const double snr = snr_ws[b];
+        double snr = snr_ws[b * PER];
+        if (PER > 1) {
+            double prod = snr;
+#pragma unroll
+            for (int w = 1; w < PER; ++w) prod *= snr_ws[b * PER + w];
+            snr = prod / (1.0 - prod);
+        }
         int f;
         const int sc = a.is_shortcut ? a.is_shortcut[l] : 0;
         const bool snr_low = a.snr_gate_on ? (snr < a.s_lo) : false;
@@ -490,7 +504,10 @@ extern "C" int cham_build_act_lut(const cham_act_stats* st, const cham_schedule*
     a.snr_gate_on = sch->snr_gate_on;
     const int n = st->L * st->B;
     (void)n;
-    hipLaunchKernelGGL(lut_kernel, dim3(1), dim3(kLutThreads), 0, (hipStream_t)stream, a);
+    if (lut_wavefronts(a.B, a.T) == 4)
+        hipLaunchKernelGGL(lut_kernel<4>, dim3(1), dim3(kLutThreads), 0, (hipStream_t)stream, a);
+    else
+        hipLaunchKernelGGL(lut_kernel<1>, dim3(1), dim3(kLutThreads), 0, (hipStream_t)stream, a);
     CHAM_CHECK_LAUNCH();
     return CHAM_OK;
 }

@@ -218,6 +218,26 @@ def test_lut_full_stack_kurtosis_only_one_bucket():
     _check_lut(lut, F, S, Z, kap)
 
 
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 16, 17])
+@pytest.mark.parametrize("T", [17, 999, 1000, 1500, 1999, 2000])
+def test_lut_snr_gate_few_buckets(B, T):
+    """Buckets whose SNR one and several wavefronts form, schedules shorter and longer than their
+    lanes: rows of kurtosis 1 (all INT8-asym above the gate) whose route turns on the SNR."""
+    x = np.tile(np.array([-1.0, 1.0], np.float32), 32).reshape(1, 64)
+    st, ost = cham.alloc_stats(2, B, DEV), oracle.Stats(2, B)
+    cham.act_stats_reset(st)
+    n = 2 * B
+    layers, buckets = [i // B for i in range(n)], [i % B for i in range(n)]
+    cham.act_stats_accumulate_batch([torch.from_numpy(x).to(DEV)] * n, layers, buckets, st)
+    for l, b in zip(layers, buckets):
+        ost.accumulate(x, l, b)
+    case(f"build_act_lut B={B} T={T}")
+    for lo, hi in ((0.2, 2.0), (1e-3, 30.0)):
+        lut = cham.build_act_lut(st, cham.Schedule(T=T, snr_lo=lo, snr_hi=hi))
+        F, S, Z, _ = oracle.build_lut(ost, (T, *oracle.BETAS_SDXL[1:]), gates=(3.0, 5.0, lo, hi))
+        assert np.array_equal(_np(lut.F), F) and np.array_equal(_np(lut.S), S) and np.array_equal(_np(lut.Z), Z)
+
+
 def _diag():
     if not os.path.exists(DIAG):
         from tests.native import build_diag
