@@ -144,10 +144,11 @@ def test_colsq_accumulate():
 
 
 @pytest.mark.parametrize("mask", [cham.MASK_DIT_W4, 0x1FF])
-@pytest.mark.parametrize("N,K", [(1, 32), (5, 288), (4, 608), (2, 7904)])
+@pytest.mark.parametrize("N,K", [(1, 32), (5, 288), (4, 608), (2, 7904), (7, 2880), (5, 2944), (5, 3936),
+                                 (3, 5920), (2, 8192)])
 def test_group_search_edges(mask, N, K):
     """One block, whole and short last groups of every size, rows of one and of several
-    staging passes; groups that are zero, constant, one-sided, subnormal and large
+    staging passes, rows whose workgroup holds over 64 KB of LDS with its static part; groups that are zero, constant, one-sided, subnormal and large
     (+-1e38: the range hi - lo must stay finite, or the INT-asym errors are NaN by definition)."""
     W, _ = synth.hetero_weights(3 * N + K, N, K)
     W[0, :32] = 0.0
