@@ -131,3 +131,54 @@ def test_conv3x3_int8_zero_point_with_a_fraction():
     Yr, Bm = oracle.conv3x3(xh, Wh)
     rel = np.abs(Y - Yr.reshape(-1, Co)) / np.maximum(Bm.reshape(-1, Co), 1e-300)
     assert rel.max() <= 1e-3, rel.max()
+
+
+T256, T128, T64 = (128, 256), (128, 128), (64, 128)
+
+
+@pytest.mark.parametrize("B,H,W,C,Co,mask,tile,splits", [
+    (2, 37, 41, 64, 4100, oracle.MASK_W4, T256, 1),
+    (2, 50, 41, 64, 3333, oracle.MASK_W8, T256, 1),
+    (2, 45, 41, 64, 2600, oracle.MASK_W4, T128, 1),
+    (2, 20, 20, 448, 1290, oracle.MASK_W4, T128, 3),
+    (2, 37, 41, 64, 777, oracle.MASK_W8, T64, 1),
+])
+@pytest.mark.parametrize("fmt", [cham.A_INT8_ASYM, cham.A_FP8_E4M3, cham.A_MXFP8, cham.A_MXINT8])
+def test_conv3x3_tiles_sampled(B, H, W, C, Co, mask, tile, splits, fmt):
+    """Every tile shape (the plan is the one named, on 256 CUs) with ragged rows and channels, a
+    k-split; INT8-asym with one image's zero point within +-1024 and the other's beyond; block scales
+    2^16 apart: sampled outputs, corners among them, against the oracle one by one."""
+    M, K = B * H * W, 9 * C
+    plan = cham.linear_plan(M, Co, K, 8 if mask == oracle.MASK_W8 else 4)
+    assert [x["tile"] for x in plan["launches"]] == [tile] and plan["splits"] == splits, plan
+    g = np.random.default_rng(M + Co)
+    X = g.standard_t(4, (B, H * W * C)).astype(np.float32)
+    if fmt == cham.A_INT8_ASYM:
+        X[1] = np.float32(30.0) + X[1] / np.abs(X[1]).max()
+    X = X.reshape(M, C)
+    if fmt in (cham.A_MXFP8, cham.A_MXINT8):
+        X *= np.exp2(g.integers(-8, 9, (M, C // 32))).repeat(32, axis=1).astype(np.float32)
+    Wt, _ = synth.hetero_weights(8, Co, K)
+    case(f"conv3x3 tiles B={B} H={H} W={W} C={C} Co={Co} mask={mask:#x} fmt={fmt}")
+    wq = cham.select_weight_formats(torch.from_numpy(Wt).to(DEV), mask, want_packed=True)
+    xq = cham.quantize_act(torch.from_numpy(X).to(DEV), fmt, dynamic=True, nsamples=B)
+    Y = _np(cham.conv3x3_mixed(xq, B, H, W, wq))
+    _, _, xh, _, z = oracle.quantize_act_per_sample(X, fmt, B, want_xhat=True)
+    assert fmt != cham.A_INT8_ASYM or (abs(z[0]) < 1024 < abs(z[1]))
+    S = 1200
+    pix, nn = g.integers(0, M, S), g.integers(0, Co, S)
+    pix[:4] = [0, W - 1, H * W - 1, M - W]  # corners: padding on two sides
+    nn[4:6] = [Co - 1, 0]
+    pix[6:8] = [M - 1, 0]
+    chans = np.unique(nn)
+    Wh = np.zeros((Co, K), np.float32)
+    Wh[chans] = oracle.dequant_weights(oracle.select_weight_formats(Wt[chans], mask, want_err=False, want_perm=False), K)
+    xp = np.zeros((B, H + 2, W + 2, C), np.float32)
+    xp[:, 1:-1, 1:-1] = xh.reshape(B, H, W, C)
+    b, rem = pix // (H * W), pix % (H * W)
+    y, x = rem // W, rem % W
+    cols = np.concatenate([xp[b, y + ky, x + kx] for ky in range(3) for kx in range(3)], axis=1)
+    Yr, Bm = oracle.linear_pairs(cols, Wh, np.arange(S), nn)
+    # 2^-11 per half-precision weight and, beyond +-1024, activation
+    rel = np.abs(Y[pix, nn].astype(np.float64) - Yr) / np.maximum(Bm, 1e-300)
+    assert rel.max() <= 1e-3, rel.max()

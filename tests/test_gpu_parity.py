@@ -629,29 +629,51 @@ def test_linear_full_size_sampled():
             assert np.all(err <= 1e-3 * bm), (name, afmt, (err / bm).max())
 
 
-@pytest.mark.parametrize("M,N,K,mask,afmt", [
-    (1500, 3000, 2560, oracle.MASK_W4, cham.A_FP8_E5M2),   # 128-row tiles, 3 k-splits, ragged M
-    (1500, 3000, 2560, oracle.MASK_W8, cham.A_INT8_ASYM),  # 8-bit codes, 256-row tiles, 3 k-splits
-    (3000, 4000, 1280, oracle.MASK_W8, cham.A_MXFP8),      # 8-bit codes, 256-row tiles, MX activations
-    (3000, 4000, 1280, oracle.MASK_W4, cham.A_MXINT8),     # 128-row tiles, MX activations
-    (8192, 4608, 1152, oracle.MASK_W8, cham.A_FP8_E4M3),   # two launches: 256-row then 128-row tiles
-    (1000, 1000, 1280, oracle.MASK_W4, cham.A_FP8_E4M3),   # 64 x 128 tiles, ragged M and N
-    (1024, 1280, 1280, oracle.MASK_W4, cham.A_FP8_E5M2),   # 64 x 128 tiles: the single-step out-projection
-    (1040, 1200, 1216, oracle.MASK_W4, cham.A_MXINT8),     # 64 x 128 tiles, MX activations, ragged M and N
-    (700, 777, 1280, oracle.MASK_W8, cham.A_INT8_ASYM),    # half-width tiles, 8-bit codes, 5 k-splits
-    (240, 1152, 4096, oracle.MASK_W4, cham.A_FP8_E4M3),    # PixArt-like cross-attn KV: 240 rows, 8 k-splits
-    (4096, 5120, 640, oracle.MASK_W4, cham.A_INT8_ASYM),   # 640-wide GEGLU at 4096 tokens
-    (1024, 1280, 5120, oracle.MASK_W4, cham.A_FP8_E5M2),   # 1280-wide FF-out at 1024 tokens
-    (2048, 1280, 5120, oracle.MASK_W4, cham.A_INT8_ASYM),  # the sweep's FF-out: 3 k-splits, XCD-aware order
-    (1300, 2000, 4096, oracle.MASK_W8, cham.A_INT8_ASYM),  # XCD-aware order over 11 x 16 tiles, ragged M and N
-    (1300, 2000, 4096, oracle.MASK_W4, cham.A_MXFP8),      # the same with MX activations
+T256, T128, T64 = (128, 256), (128, 128), (64, 128)
+
+
+@pytest.mark.parametrize("M,N,K,mask,afmt,tile,splits", [
+    (1500, 3000, 2560, oracle.MASK_W4, cham.A_FP8_E5M2, T128, 1),   # ragged M and N, row-major order
+    (1500, 3000, 2560, oracle.MASK_W8, cham.A_INT8_ASYM, T128, 1),  # 8-bit codes
+    (3000, 4000, 1280, oracle.MASK_W8, cham.A_MXFP8, T128, 1),      # 8-bit codes, MX activations
+    (3000, 4000, 1280, oracle.MASK_W4, cham.A_MXINT8, T128, 1),
+    (8192, 4608, 1152, oracle.MASK_W8, cham.A_FP8_E4M3, T256, 1),   # whole tiles, the DiT MLP
+    (1000, 1000, 1280, oracle.MASK_W4, cham.A_FP8_E4M3, T64, 1),    # ragged M and N
+    (1024, 1280, 1280, oracle.MASK_W4, cham.A_FP8_E5M2, T64, 1),    # the single-step out-projection
+    (1040, 1200, 1216, oracle.MASK_W4, cham.A_MXINT8, T64, 1),      # MX activations, ragged M and N
+    (700, 777, 1280, oracle.MASK_W8, cham.A_INT8_ASYM, T64, 1),     # 8-bit codes
+    (240, 1152, 4096, oracle.MASK_W4, cham.A_FP8_E4M3, T64, 6),     # PixArt-like cross-attn KV
+    (4096, 5120, 640, oracle.MASK_W4, cham.A_INT8_ASYM, T128, 1),   # 640-wide GEGLU at 4096 tokens
+    (1024, 1280, 5120, oracle.MASK_W4, cham.A_FP8_E5M2, T128, 3),   # 1280-wide FF-out at 1024 tokens
+    (2048, 1280, 5120, oracle.MASK_W4, cham.A_INT8_ASYM, T128, 3),  # the sweep's FF-out
+    (1300, 2000, 4096, oracle.MASK_W8, cham.A_INT8_ASYM, T128, 1),  # 11 x 16 tiles, ragged M and N
+    (1300, 2000, 4096, oracle.MASK_W4, cham.A_MXFP8, T128, 1),      # the same with MX activations
+    (1000, 3072, 768, oracle.MASK_W4, cham.A_FP8_E4M3, T64, 1),     # row-major order over 24 columns
+    (333, 500, 1920, oracle.MASK_W4, cham.A_MXFP8, T64, 6),         # k-split, MX activations, ragged
+    (500, 777, 1920, oracle.MASK_W8, cham.A_MXINT8, T64, 4),
+    (1300, 777, 4096, oracle.MASK_W4, cham.A_MXINT8, T128, 3),
+    (3001, 4099, 640, oracle.MASK_W4, cham.A_FP8_E5M2, T256, 1),    # ragged M and N, lines cut anywhere
+    (2999, 5121, 640, oracle.MASK_W8, cham.A_INT8_ASYM, T256, 1),
+    (2999, 5121, 640, oracle.MASK_W4, "far", T256, 1),              # INT8-asym, zero point beyond +-1024
+    (4003, 3333, 640, oracle.MASK_W4, cham.A_MXFP8, T256, 1),
+    (4003, 3333, 640, oracle.MASK_W8, cham.A_MXINT8, T256, 1),
+    (1301, 3333, 4096, oracle.MASK_W8, "far", T256, 3),             # with a k-split
+    (1001, 4100, 4096, oracle.MASK_W4, cham.A_FP8_E5M2, T256, 3),
+    (5001, 777, 4096, oracle.MASK_W4, cham.A_MXFP8, T256, 3),
+    (3001, 1290, 4096, oracle.MASK_W4, cham.A_MXINT8, T256, 3),
 ])
-def test_linear_plans_sampled(M, N, K, mask, afmt):
-    """Tile heights, k-splits and two-launch plans the sizes above select (each code width,
-    per-tensor and MX activations): sampled outputs against the oracle one by one."""
+def test_linear_plans_sampled(M, N, K, mask, afmt, tile, splits):
+    """Every tile shape, with and without a k-split, per-tensor and MX activations and both code
+    widths: the plan is the one named (on 256 CUs), sampled outputs against the oracle one by one."""
+    plan = cham.linear_plan(M, N, K, 8 if mask == oracle.MASK_W8 else 4)
+    assert [(x["rows"], x["tile"]) for x in plan["launches"]] == [((0, M), tile)] and plan["splits"] == splits, plan
     X = synth.diffusion_acts(5, 2, 600, M, K)
+    far = afmt == "far"
+    if far:
+        afmt = cham.A_INT8_ASYM
+        X = np.float32(30.0) + X / np.abs(X).max()
     W, _ = synth.hetero_weights(31, N, K)
-    case(f"mixed_linear plan M={M} N={N} K={K} mask={mask:#x} afmt={afmt}")
+    case(f"mixed_linear plan M={M} N={N} K={K} mask={mask:#x} afmt={afmt} far={far}")
     wq = cham.select_weight_formats(torch.from_numpy(W).to(DEV), mask, want_packed=True)
     xq = cham.quantize_act(torch.from_numpy(X).to(DEV), afmt, dynamic=True)
     Y = _np(cham.mixed_linear(xq, wq)).astype(np.float64)
@@ -668,6 +690,7 @@ def test_linear_plans_sampled(M, N, K, mask, afmt):
     mrows = np.unique(mm)
     lo, hi = oracle.minmax(X)  # the whole tensor's range (MX formats: s = 1, z = 0)
     s, z = oracle.scale_zp(afmt, lo, hi)
+    assert not far or abs(z) > 1024
     xh = np.zeros_like(X)
     xh[mrows] = oracle.quantize_act(X[mrows], afmt, s, z, want_xhat=True)[2]
     yr, bm = oracle.linear_pairs(xh, Wh, mm, nn)
@@ -879,9 +902,12 @@ def test_linear_random_shapes(seed):
 def test_search_batch_long_and_short_rows_share_a_launch(mask):
     """Rows of at most 1280 elements beside rows of up to 5120 in one batch, in either order, with
     whole and partial last workgroups: the outputs are those of one call per layer."""
-    shapes = [(1030, 832), (1026, 2624), (1033, 1280), (1024, 5120)]
+    shapes = [(1030, 832), (1026, 2624), (1033, 1280), (1024, 5120), (1024, 2624), (1024, 832)]
     Ws = [torch.from_numpy(synth.hetero_weights(60 + i, N, K)[0]).to(DEV) for i, (N, K) in enumerate(shapes)]
-    for order in ((0, 1, 2), (3, 0), (2, 1, 3), (1, 3)):  # the third: too many long rows to share
+    # (2, 1, 3): too many long rows to share; (4, 3, 5): the most, short ones of a ninth of their weights
+    # share with every palette; (2, 4, 0, 3): of a third, not with one read at run time; the last: more
+    # layers than a launch takes, long ones past its end
+    for order in ((0, 1, 2), (3, 0), (2, 1, 3), (1, 3), (4, 3, 5), (2, 4, 0, 3), (0, 2) * 8 + (4, 5, 4)):
         case(f"select_weight_formats_batch mask={mask:#x} layers={order}")
         outs = cham.select_weight_formats_batch([Ws[i] for i in order], mask)
         for i, o in zip(order, outs):
