@@ -103,10 +103,11 @@ def search_bytes(N: int, K: int, bits: int = 4) -> float:
 
 
 def pack_bytes(N: int, K: int) -> float:
-    """Algorithmic bytes of the packing pass: codes and block metadata read (once for the
-    records, once for the column sums), 48 B of record per 32 weights written, 20 B per
-    channel."""
-    return N * K * (2 * (0.5 + 4.0 / 64 + 1.0 / 32) + 1.5) + 20.0 * N
+    """Algorithmic bytes of the packing pass: codes and block metadata read once (the pass reads
+    the metadata a second time, for the channel's reference exponent), 2 B written per weight (its
+    half-precision operand), 29 B per channel (format, scale and zero point read, parameters and
+    column sum written)."""
+    return N * K * (0.5 + 4.0 / 64 + 1.0 / 32 + 2.0) + 29.0 * N
 
 
 def main():

@@ -424,12 +424,11 @@ int cham_conv3x3_mixed(const cham_aq* xq, int32_t B, int32_t H, int32_t W, const
  * (0 for sizes out of range). */
 size_t cham_conv3x3_workspace_bytes(int64_t B, int64_t H, int64_t W, int64_t C, int64_t Co);
 
-/* The launch plan cham_mixed_linear takes for M x N x K with 4- or 8-bit weight codes
- * (diagnostics; host only, launches nothing).  out (host, out_len >= 10 int32) receives
- * {launches (1 or 2), k-splits, then per launch: first row, end row, tile rows, tile
- * channels}; entries of an absent second launch are 0.  The plan depends on the current
- * device's CU count (256 when no device is visible).  Errors: CHAM_EINVAL (NULL out,
- * out_len < 10, sizes < 1, code_bits not 4 or 8). */
+/* The launch plan cham_mixed_linear takes for M x N x K (diagnostics; host only, launches
+ * nothing).  out (host, out_len >= 10 int32) receives {launches, always 1; k-splits; first row 0,
+ * end row M, tile rows, tile channels; four zeros}.  code_bits (4 or 8) is checked and does not
+ * change the plan.  The plan depends on the current device's CU count (256 when no device is
+ * visible).  Errors: CHAM_EINVAL (NULL out, out_len < 10, sizes < 1, code_bits not 4 or 8). */
 int cham_linear_plan(int64_t M, int64_t N, int64_t K, int32_t code_bits, int32_t* out, int32_t out_len);
 
 /* ---------------------------------------------------------------------------------------

@@ -17,18 +17,22 @@
 // Activations are decoded to half precision while they are staged into LDS: per-tensor formats
 // (INT8, E4M3, E5M2) exactly, MX formats relative to the largest block exponent of the row
 // (3x3 convolution: of the pixels the tile gathers), which each workgroup finds in the
-// exponent bytes first.  That adds 3 us to the MXFP8 product 8100 x 640 x 1920 (29.9 -> 32.9)
-// and 5 to the convolution 1920 -> 640 at 2 x 32 x 32 (49.8 -> 54.9); the pre-passes that wrote
-// a half-precision copy instead took 13.7 and 38.8 us.
+// exponent bytes first, once per tile column.  That adds 3 us to the MXFP8 product
+// 8100 x 640 x 1920 (29.9 -> 32.9) and 5 to the convolution 1920 -> 640 at 2 x 32 x 32
+// (49.8 -> 54.9); the pre-passes that wrote a half-precision copy instead took 13.7 and 38.8 us.
+// On wide layers too the whole call is faster than with the pre-pass (and the weights' decode in
+// the loop): 2048 x 10240 x 1280 70.6 -> 61.7 us with MXFP8, 70.0 -> 69.3 with MXINT8;
+// 8192 x 10240 x 1280 244 -> 206 and 243 -> 222.
 //
 // Main kernel: 128 x 256, 128 x 128 or 64 x 128 output tiles; k-steps of 64; four wavefronts
 // side by side that each own all the tile's rows x 32 TN channels (blocks of
-// v_mfma_f32_32x32x16_f16, binary32 accumulation).  What bounds it: on long layers power (a
-// 4096 x 4096 x 16384 product runs at 1314 TFLOP/s with the matrix cores busy 74 % of the
-// cycles at 1.65 GHz, as the library's dense f16 product does, 1290), on short ones the rounds
-// of tiles that do not fill the chip and the output write.  Per k-step a 128 x 64 wavefront
-// block reads 16 KB from LDS and 8 KB from L1 for 1024 MFMA cycles per SIMD, about half of
-// either's rate; the 128 x 32 block reads twice as much LDS per MFMA, and three of them per
+// v_mfma_f32_32x32x16_f16, binary32 accumulation).  What bounds it: on long layers the matrix
+// cores, at the clock that such a load leaves them (a 4096 x 4096 x 16384 product runs at 1273
+// TFLOP/s with them busy 75 % of the cycles at 1.55 GHz; the library's dense f16 product, both
+// operands in the memory order of k, at 1481 - 1572, busy 88 % at 1.51 GHz), on short ones the
+// rounds of tiles that do not fill the chip and the output write.  Per k-step a 128 x 64
+// wavefront block reads 16 KB from LDS and 8 KB from L1 for 1024 MFMA cycles per SIMD, about half
+// of either's rate; the 128 x 32 block reads twice as much LDS per MFMA, and three of them per
 // SIMD hide latency better.
 // Weights go from memory straight to the operand registers (coalesced 16-byte buffer loads, a
 // step or two ahead); activation tiles go global -> registers -> one of two LDS buffers, with
@@ -161,11 +165,11 @@ struct RecArgs {
 
 // Workgroup b handles 32 channels (block b % nblk) and the k-steps of chunk b / nblk.
 // 8 threads per channel compute its ColPrep (the reference exponent is the largest NF4
-// block absmax or MX block exponent of the whole channel); thread t builds the records of
-// channel t/2 % 32, half t % 2, at k-steps congruent to t/64 mod 4, so each wavefront
-// stores 64 consecutive records (coalesced).  The codes and block metadata of the
-// thread's first kRecPrefetch records are loaded before the ColPrep pass, so both
-// passes' loads are in flight together.
+// block absmax or MX block exponent of the whole channel); thread t decodes the records of
+// channel t % 32, half t / 32 % 2, at k-steps congruent to t / 64 mod 4, so each wavefront
+// stores 1 KB in a row per sub-step.  The codes and block metadata of the thread's first
+// kRecPrefetch records are loaded before the ColPrep pass, so both passes' loads are in
+// flight together.
 constexpr int kRecChannels = 32;
 constexpr int kRecPrefetch = 3;
 
@@ -915,12 +919,15 @@ int cu_count() {
 // Modeled time (us) of a launch of one tile shape: a fixed cost (prologue, tail), plus the
 // k-steps of the rounds of workgroups, each at the k-step time of as many workgroups per CU as
 // the round puts there -- the workgroups of later rounds start while earlier ones finish --
-// plus the output.  The numbers are fitted to 1720 forced plans over 180 shapes (M 200 - 8192,
-// N 320 - 10240, K 640 - 5120) on MI355X, each timed behind its quantize call and again with
-// the last-level cache swept by other data; the planner's choice takes 1.0 % longer than the
-// best of the forced plans on average, 15 % at worst.  Tiles measured and not kept, as no shape
-// ran faster in them: 256 x 256 (one wavefront per SIMD: 84 us against 56 on
-// 2048 x 10240 x 1280), 64 x 256, and 128 x 128 and 64 x 128 of two wavefronts.
+// plus the output.  The numbers are fitted to 1720 forced plans of per-tensor layers over 180
+// shapes (M 200 - 8192, N 320 - 10240, K 640 - 5120) on MI355X, each timed behind its quantize call
+// and again with the last-level cache swept by other data; there the planner's choice takes 1.0 %
+// longer than the best of the forced plans on average, 15 % at worst.  MX activations and the
+// convolution take the same plans although their staging costs more: over 49 shapes, two
+// sets of operands in turn, the choice takes 1.4 (E4M3), 1.7 (INT8), 3.3 (MXFP8) and 3.6 % (MXINT8) longer than the
+// best on average and 6, 12, 20 and 26 % at worst; over 9 convolutions 4 - 8 % and 16 %.  Tiles
+// measured and not kept, as no shape ran faster in them: 256 x 256 (one wavefront per SIMD: 84 us
+// against 56 on 2048 x 10240 x 1280), 64 x 256, and 128 x 128 and 64 x 128 of two wavefronts.
 constexpr int kMaxOcc = 4;
 struct TileCost {
     int tm, tn, nw, occ;   // 32-row blocks, 32-channel blocks per wavefront, wavefronts, workgroups per CU
@@ -1045,7 +1052,8 @@ static void rec_chunks(int64_t N, int64_t K, int* nkc, int* rchunk) {
     *nkc = (nst + *rchunk - 1) / *rchunk;
 }
 
-// The packed layout: ColPrep[N], the column-sum partials [k-chunks][N], then the records.
+// The packed layout: ColPrep[N], the column-sum partials [k-chunks][N], then the half-precision
+// weights.
 extern "C" size_t cham_packed_bytes(int64_t N, int64_t K) {
     if (N < 1 || K < 64) return 0;
     int nkc, rchunk;
@@ -1252,8 +1260,8 @@ static int mixed_linear_impl(const cham_aq* xq, const WView& v, float* Y, void* 
     if (wq->code_bits != code_bits) return CHAM_EFORMAT;
     if (wq->gsel && code_bits != 4) return CHAM_EFORMAT;  // the 8-bit group-scaled decode is not built
     if (wq->K % 64 != 0) return CHAM_ESHAPE;
-    // 32-bit buffer offsets: a 256-row activation tile, a 256-row output tile and the
-    // weight records stay below 2^31 bytes
+    // 32-bit buffer offsets: an activation tile and an output tile of 256 rows (the tiles have 128
+    // at most) and the half-precision weights stay below 2^31 bytes
     if (xq->M > INT32_MAX / 2 || wq->N > INT32_MAX / 1024 || wq->K > (1 << 20) ||
         wq->N * (wq->K / BK) * 128 > (int64_t)INT32_MAX)
         return CHAM_ESHAPE;

@@ -152,23 +152,17 @@ def test_binding_fails_loudly_without_library(monkeypatch, tmp_path):
 
 
 def test_linear_plans_are_valid():
-    """The GEMM planner on the host (no GPU: 256 CUs assumed): for a grid of shapes the
-    launches tile the rows in order with shapes the kernels exist for, every k-split holds
-    at least one k-step, only single launches split k, and the workspace the library asks
-    for holds the split partial outputs."""
+    """The GEMM planner on the host (no GPU: 256 CUs assumed): for a grid of shapes one launch
+    over all rows, of a tile the kernels exist for, the same for 4- and 8-bit codes; every k-split
+    holds at least one k-step, and the workspace the library asks for holds the partial outputs."""
     for M in (1, 7, 64, 240, 1000, 2048, 4096, 8192):
         for N in (32, 640, 777, 1280, 3840, 10240):
             for K in (64, 640, 1280, 5120):
                 for bits in (4, 8):
                     p = cham.linear_plan(M, N, K, bits)
-                    ls = p["launches"]
-                    assert 1 <= len(ls) <= 2, (M, N, K, bits, p)
-                    assert ls[0]["rows"][0] == 0 and ls[-1]["rows"][1] == M, p
-                    if len(ls) == 2:
-                        assert ls[0]["rows"][1] == ls[1]["rows"][0] and p["splits"] == 1, p
-                    for l in ls:
-                        assert l["rows"][0] < l["rows"][1], p
-                        assert l["tile"] in ((256, 256), (128, 256), (128, 128), (64, 256), (64, 128)), p
+                    assert p == cham.linear_plan(M, N, K, 12 - bits)
+                    assert [l["rows"] for l in p["launches"]] == [(0, M)], (M, N, K, bits, p)
+                    assert p["launches"][0]["tile"] in ((128, 256), (128, 128), (64, 128)), p
                     steps, sp = K // 64, p["splits"]
                     assert 1 <= sp <= 8, p
                     chunk = -(-steps // sp)
@@ -184,7 +178,7 @@ def test_linear_plans_are_valid():
 def test_linear_workspace_query_on_the_host():
     """The exact-workspace query checks the operands like mixed_linear, launches nothing and
     reads no device memory: the decode layout without a packed one, nothing with it (FP8
-    activations, no split at these sizes), the half-precision copy and row scales for MX."""
+    activations, no split at these sizes), room of a half-precision copy and row scales for MX."""
     L = cham.lib()
     P = ctypes.c_void_p
     nb = ctypes.c_size_t(12345)

@@ -277,7 +277,7 @@ def test_rcp_rn_equals_ieee_quotient_everywhere():
                                                 (cham.A_MXFP8, False, 2048, 1280, 5120),
                                                 (cham.A_INT8_ASYM, False, 300, 200, 640)])
 def test_linear_exact_workspace(afmt, packed, M, N, K):
-    """The workspace query names exactly what the call uses: the half-precision copy and
+    """The workspace query names exactly what the call takes: room of a half-precision copy and
     row scales only for MX activations, the weight layout only without a packed layout, the
     partials only when the plan splits K; one byte less is refused before any launch, and
     the output equals the one computed with the CHAM_OP_LINEAR upper bound."""
