@@ -923,11 +923,12 @@ int cu_count() {
 // shapes (M 200 - 8192, N 320 - 10240, K 640 - 5120) on MI355X, each timed behind its quantize call
 // and again with the last-level cache swept by other data; there the planner's choice takes 1.0 %
 // longer than the best of the forced plans on average, 15 % at worst.  MX activations and the
-// convolution take the same plans although their staging costs more: over 49 shapes, two
-// sets of operands in turn, the choice takes 1.4 (E4M3), 1.7 (INT8), 3.3 (MXFP8) and 3.6 % (MXINT8) longer than the
-// best on average and 6, 12, 20 and 26 % at worst; over 9 convolutions 4 - 8 % and 16 %.  Tiles
-// measured and not kept, as no shape ran faster in them: 256 x 256 (one wavefront per SIMD: 84 us
-// against 56 on 2048 x 10240 x 1280), 64 x 256, and 128 x 128 and 64 x 128 of two wavefronts.
+// convolution take the same plans although their staging costs more: over 49 shapes, two sets of
+// operands in turn, the choice takes 0.7 (E4M3), 1.0 (INT8), 2.5 (MXFP8) and 3.1 % (MXINT8) longer
+// than the best on average and 7, 12, 20 and 25 % at worst; over 9 convolutions 2.0 (MXFP8), 2.4
+// (E4M3) and 5.5 % (INT8), 14 % at worst.  Tiles measured and not kept, as no shape ran faster in
+// them: 256 x 256 (one wavefront per SIMD: 84 us against 56 on 2048 x 10240 x 1280), 64 x 256, and
+// 128 x 128 and 64 x 128 of two wavefronts.
 constexpr int kMaxOcc = 4;
 struct TileCost {
     int tm, tn, nw, occ;   // 32-row blocks, 32-channel blocks per wavefront, wavefronts, workgroups per CU
