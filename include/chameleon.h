@@ -377,7 +377,7 @@ int cham_quantize_act_lut_accumulate_batch(const float* const* X, const int32_t*
  * are used, so Y is bitwise reproducible run to run.  If wq->packed is set it supplies the
  * weights' decode layout; otherwise a pre-pass derives it from the codes and metadata into
  * the workspace.  ws: what cham_mixed_linear_workspace_query reports for these operands
- * (room for a half-precision copy of MX activations and their row scales, the weights' layout
+ * (2 M K + 4 M bytes reserved and not written for MX activations, the weights' layout
  * when wq->packed is NULL, the k-split partial outputs when the plan splits; possibly 0,
  * then ws may be NULL), 256-byte aligned; CHAM_OP_LINEAR bytes always suffice.
  * Errors: CHAM_EINVAL, CHAM_EFORMAT, CHAM_ESHAPE, CHAM_EWORKSPACE, CHAM_EHIP.
@@ -414,9 +414,9 @@ int cham_mixed_linear_grouped_workspace_query(const cham_aq* xq, const cham_gwq*
  * out-of-image pixels zero.  The GEMM gathers the codes per output pixel and tap and decodes
  * them to half precision (MX formats relative to the largest block exponent of the pixels an
  * output tile gathers: exact for blocks within 2^28 of it; INT8-asym q - z rounded once when
- * beyond 2^11); accuracy as cham_mixed_linear.  ws: cham_conv3x3_workspace_bytes.
- * Errors: CHAM_EINVAL (sizes, pointers, samples), CHAM_EFORMAT, CHAM_ESHAPE (C % 64, a
- * zero-padded half-precision copy beyond 2^31 bytes), CHAM_EWORKSPACE, CHAM_EHIP. */
+ * beyond 2^11 or where the zero point is no integer); accuracy as cham_mixed_linear.  ws: cham_conv3x3_workspace_bytes.
+ * Errors: CHAM_EINVAL (sizes, pointers, samples), CHAM_EFORMAT, CHAM_ESHAPE (C % 64, or
+ * 2 B (H + 2) (W + 2) C beyond 2^31 - 4096), CHAM_EWORKSPACE, CHAM_EHIP. */
 int cham_conv3x3_mixed(const cham_aq* xq, int32_t B, int32_t H, int32_t W, const cham_wq* wq, float* Y,
                        void* ws, size_t ws_bytes, void* stream);
 
