@@ -414,7 +414,8 @@ int cham_mixed_linear_grouped_workspace_query(const cham_aq* xq, const cham_gwq*
  * out-of-image pixels zero.  The GEMM gathers the codes per output pixel and tap and decodes
  * them to half precision (MX formats relative to the largest block exponent of the pixels an
  * output tile gathers: exact for blocks within 2^28 of it; INT8-asym q - z rounded once when
- * beyond 2^11 or where the zero point is no integer); accuracy as cham_mixed_linear.  ws: cham_conv3x3_workspace_bytes.
+ * beyond 2^11 or where the zero point is no integer); accuracy as cham_mixed_linear.
+ * ws: cham_conv3x3_workspace_bytes.
  * Errors: CHAM_EINVAL (sizes, pointers, samples), CHAM_EFORMAT, CHAM_ESHAPE (C % 64, or
  * 2 B (H + 2) (W + 2) C beyond 2^31 - 4096), CHAM_EWORKSPACE, CHAM_EHIP. */
 int cham_conv3x3_mixed(const cham_aq* xq, int32_t B, int32_t H, int32_t W, const cham_wq* wq, float* Y,
